@@ -138,6 +138,33 @@ __device__ __noinline__ int tri_tri_filtered64(const double *A, const double *B)
     return 0;
 }
 
+// The segment p q against the closed triangle T: 1 = they meet, 0 = disjoint,
+// 2 = undecided.  Both endpoints strictly on one side of the plane: disjoint.
+// Strictly on opposite sides (so T is no degenerate triangle), the crossing
+// point's barycentric coordinates have the signs of the three orientations of
+// the line against T's directed edges, up to one common sign: all strictly
+// alike, it lies inside; two strictly opposite, outside.  The triangle-pair
+// filter above leaves every crossing segment undecided (the segment's own
+// plane has no orientation), and the exact test that settles it then costs a
+// wave some 50 us.
+__device__ __noinline__ int seg_tri_filtered64(const double *p, const double *q, const double *T) {
+    const int s0 = orient3d_f64(T, T + 3, T + 6, p);
+    if (s0 == 2) return 2;
+    const int s1 = orient3d_f64(T, T + 3, T + 6, q);
+    if (s1 == 2) return 2;
+    if (s0 == s1) return 0;
+    bool pos = false, neg = false, open = false;
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        const int o = orient3d_f64(p, q, T + 3 * k, T + 3 * ((k + 1) % 3));
+        pos |= o == 1;
+        neg |= o == -1;
+        open |= o == 2;
+    }
+    if (pos && neg) return 0;
+    return open ? 2 : 1;
+}
+
 struct Pair64 {
     double d2;   // squared distance (0 when the pair is certified to meet)
     int status;  // 0 disjoint, 1 meet, 2 undecided (d2 = distance if disjoint)
@@ -150,7 +177,9 @@ struct Pair64 {
 // of a vector between two points of the triangles (feasible parameters), all
 // vectors formed from coordinate differences first.  Disjointness is then
 // certified by the separating plane normal to the best vector; otherwise the
-// filtered intersection test decides.
+// filtered intersection test decides.  SEG: A is a segment as the triangle
+// (P0, P1, P1), and the filter is the segment's.
+template <bool SEG = false>
 __device__ __forceinline__ Pair64 pair64(TriRef<double> A, TriRef<double> B) {
     double best = __builtin_inf();
     double bx = 0.0, by = 0.0, bz = 0.0;  // best vector, from the B point to the A point
@@ -237,7 +266,7 @@ __device__ __forceinline__ Pair64 pair64(TriRef<double> A, TriRef<double> B) {
         va[i] = A[F_V + i];
         vb[i] = B[F_V + i];
     }
-    int f = tri_tri_filtered64(va, vb);
+    const int f = SEG ? seg_tri_filtered64(va, va + 3, vb) : tri_tri_filtered64(va, vb);
     if (f == 1) return {0.0, 1};
     return {best, f == 0 ? 0 : 2};
 }

@@ -222,7 +222,7 @@ __global__ __launch_bounds__(64) void k_segs(const double *seg, int64_t n, const
             if (on && !done[slot]) {
                 TriRef<double> A{sS + slot, 64};
                 TriRef<double> B{const_cast<double *>(P) + t * SEG_NF, 1};
-                const Pair64 pr = pair64(A, B);
+                const Pair64 pr = pair64<true>(A, B);
                 int st = pr.status;
                 n_full++;
                 if (st == 2) {
