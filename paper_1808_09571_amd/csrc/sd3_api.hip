@@ -164,7 +164,7 @@ struct sd3_ctx {
     void *pin = nullptr;  // pinned host staging: offsets up, counters down
     size_t pin_cap = 0;
     int pairs_grid[2][2][3] = {};         // [precision][mode][tile size 32/64/128]
-    int seg_grid[3] = {};                 // segment kernels, per operator
+    int seg_grid[3][SEG_LEVELS] = {};     // segment kernels, per operator and tree height
     std::map<uint64_t, int> tuned;        // workload key -> tile size (sd3_autotune)
     hipEvent_t ev[8] = {};
     KernelEvents *kev = nullptr;  // created on the first timed call
@@ -1142,9 +1142,13 @@ sd3_status sd3_segments(sd3_ctx *ctx, int32_t op, const double *seg, int64_t n, 
             tri = dt;
         }
         const int64_t ntiles = (nt + SEG_MESH_TILE - 1) / SEG_MESH_TILE;
-        double *P = (double *)ensure(ws.seg_mesh, sizeof(double) * (SEG_MESH_FIELDS * nt + 6 * ntiles + 6) + 64);
-        double *tbox = P + SEG_MESH_FIELDS * nt;
-        double *mbox = tbox + 6 * ntiles;
+        const SegTree T = seg_tree(nt);
+        // [nodes | triangles | mesh box]
+        char *mb = (char *)ensure(ws.seg_mesh, (size_t)SEG_NODE_BYTES * T.nodes +
+                                                   sizeof(double) * (SEG_MESH_FIELDS * nt + 6) + 64);
+        float *nodes = (float *)mb;
+        double *P = (double *)(mb + (size_t)SEG_NODE_BYTES * T.nodes);
+        unsigned long long *box = (unsigned long long *)(P + SEG_MESH_FIELDS * nt);
         unsigned int *sc = (unsigned int *)ensure(ws.scalars, SCALAR_BYTES);
         uint32_t *flags = (uint32_t *)sc;
         unsigned long long *cnt = (unsigned long long *)(sc + 16);
@@ -1155,22 +1159,18 @@ sd3_status sd3_segments(sd3_ctx *ctx, int32_t op, const double *seg, int64_t n, 
             odist = dist ? (double *)o : nullptr;
             oflag = flag ? (uint8_t *)(o + sizeof(double) * (n > 0 ? n : 1)) : nullptr;
         }
-        launch_seg_validate(dseg, n, xyz, nv, tri, nt, flags, cnt, s);
+        // the contents of device inputs are checked by the first kernel; the
+        // others clamp every index into the mesh and write no result while a
+        // flag is set, so that the flags are read with the counters at the end
+        launch_seg_validate(dseg, n, xyz, nv, tri, nt, flags, cnt, box, s);
         ensure_pinned(ctx, 0);
         char *rb = readback_area(ctx);
-        if (seg_mem == SD3_MEM_DEVICE) {
-            // device inputs are validated before any kernel reads them
-            check(hipMemcpyAsync(rb, sc, 64, hipMemcpyDeviceToHost, s), "D2H flags");
-            check(hipStreamSynchronize(s), "sync");
-            const uint32_t f = ((const uint32_t *)rb)[0] | ((const uint32_t *)rb)[1];
-            if (f & V_NONFINITE) return fail(ctx, SD3_E_NONFINITE, "non-finite coordinate");
-            if (f & V_RANGE) return fail(ctx, SD3_E_RANGE, "coordinate magnitude outside [2^-256, 2^256]");
-            if (f & V_INDEX) return fail(ctx, SD3_E_INDEX_RANGE, "triangle index outside the mesh");
-        }
-        launch_seg_mesh(xyz, nv, tri, nt, P, tbox, mbox, s);
-        int &gp = ctx->seg_grid[mode];
-        if (gp == 0) gp = ctx->cus * seg_blocks_per_cu(mode);
-        launch_segs(mode, dseg, n, P, nt, tbox, mbox, r, mode == 0 ? odist : nullptr, oflag, flags, cnt, gp, s);
+        launch_seg_mesh(xyz, nv, tri, nt, T, box, P, nodes, s);
+        int &gp = ctx->seg_grid[mode][T.top];
+        // four blocks for each that is resident: the waves' work differs, and
+        // a finished one makes room for the next
+        if (gp == 0) gp = 4 * ctx->cus * seg_blocks_per_cu(mode, T);
+        launch_segs(mode, dseg, n, P, nt, T, nodes, box, r, mode == 0 ? odist : nullptr, oflag, flags, cnt, gp, s);
         check(hipGetLastError(), "kernel launch");
         check(hipMemcpyAsync(rb, sc, SCALAR_BYTES, hipMemcpyDeviceToHost, s), "D2H counters");
         if (seg_mem == SD3_MEM_HOST && n > 0) {
@@ -1178,6 +1178,10 @@ sd3_status sd3_segments(sd3_ctx *ctx, int32_t op, const double *seg, int64_t n, 
             if (flag) check(hipMemcpyAsync(flag, oflag, n, hipMemcpyDeviceToHost, s), "D2H flags");
         }
         check(hipStreamSynchronize(s), "sync");
+        const uint32_t f = ((const uint32_t *)rb)[0] | ((const uint32_t *)rb)[1];
+        if (f & V_NONFINITE) return fail(ctx, SD3_E_NONFINITE, "non-finite coordinate");
+        if (f & V_RANGE) return fail(ctx, SD3_E_RANGE, "coordinate magnitude outside [2^-256, 2^256]");
+        if (f & V_INDEX) return fail(ctx, SD3_E_INDEX_RANGE, "triangle index outside the mesh");
         const unsigned long long *cnt_h = (const unsigned long long *)(rb + 64);
         if (stats) {
             memset(stats, 0, sizeof(*stats));

@@ -177,9 +177,7 @@ struct Pair64 {
 // of a vector between two points of the triangles (feasible parameters), all
 // vectors formed from coordinate differences first.  Disjointness is then
 // certified by the separating plane normal to the best vector; otherwise the
-// filtered intersection test decides.  SEG: A is a segment as the triangle
-// (P0, P1, P1), and the filter is the segment's.
-template <bool SEG = false>
+// filtered intersection test decides.
 __device__ __forceinline__ Pair64 pair64(TriRef<double> A, TriRef<double> B) {
     double best = __builtin_inf();
     double bx = 0.0, by = 0.0, bz = 0.0;  // best vector, from the B point to the A point
@@ -266,7 +264,106 @@ __device__ __forceinline__ Pair64 pair64(TriRef<double> A, TriRef<double> B) {
         va[i] = A[F_V + i];
         vb[i] = B[F_V + i];
     }
-    const int f = SEG ? seg_tri_filtered64(va, va + 3, vb) : tri_tri_filtered64(va, vb);
+    int f = tri_tri_filtered64(va, vb);
+    if (f == 1) return {0.0, 1};
+    return {best, f == 0 ? 0 : 2};
+}
+
+// A prepared triangle of the segment path: its vertices and the derived
+// fields that cost a division (the edges and their squared lengths are formed
+// again from the vertices, to the same bits).
+enum : int { S_V = 0, S_IE = 9, S_G1 = 12, S_G2 = 15, S_NTRI = 18 };
+
+// pair64 of the degenerate triangle (p, q, q) and T, to the same bits: of the
+// 15 candidates those that differ are formed -- the segment against each edge
+// from p and from q (the reversed edge's dot products are exact negations),
+// q against each edge, p and q against the face, p against each vertex (the
+// degenerate face's barycentric coordinates are 0).
+__device__ __forceinline__ Pair64 seg_pair64(const double (&p)[3], const double (&q)[3], const double *T) {
+    double best = __builtin_inf();
+    double bx = 0.0, by = 0.0, bz = 0.0;  // best vector, from T's point to the segment's
+    double v[9];
+#pragma unroll
+    for (int i = 0; i < 9; i++) v[i] = T[S_V + i];
+    const double ux = q[0] - p[0], uy = q[1] - p[1], uz = q[2] - p[2];
+    const double a = dot3d(ux, uy, uz, ux, uy, uz), ia = a > 0.0 ? 1.0 / a : 0.0;
+    double sx[3], sy[3], sz[3];  // p - v_l
+    double tx[3], ty[3], tz[3];  // q - v_l
+    auto take = [&](double w, double x, double y, double z) __attribute__((always_inline)) {
+        if (w < best) {
+            best = w;
+            bx = x;
+            by = y;
+            bz = z;
+        }
+    };
+#pragma unroll
+    for (int l = 0; l < 3; l++) {
+        const int m = (l + 1) % 3;
+        const double vx = v[3 * m] - v[3 * l], vy = v[3 * m + 1] - v[3 * l + 1], vz = v[3 * m + 2] - v[3 * l + 2];
+        const double c = dot3d(vx, vy, vz, vx, vy, vz), ic = T[S_IE + l];
+        sx[l] = p[0] - v[3 * l];
+        sy[l] = p[1] - v[3 * l + 1];
+        sz[l] = p[2] - v[3 * l + 2];
+        tx[l] = q[0] - v[3 * l];
+        ty[l] = q[1] - v[3 * l + 1];
+        tz[l] = q[2] - v[3 * l + 2];
+        const double bb = dot3d(ux, uy, uz, vx, vy, vz);
+        const double D = fma(a, c, -(bb * bb));
+        {  // the edge p -> q
+            const double d = dot3d(ux, uy, uz, sx[l], sy[l], sz[l]), e = dot3d(vx, vy, vz, sx[l], sy[l], sz[l]);
+            double s = 0.0;
+            if (D > 0.0) s = clamp01d(fma(bb, e, -(c * d)) / D);
+            const double t = clamp01d(fma(bb, s, e) * ic);
+            s = clamp01d(fma(bb, t, -d) * ia);
+            const double wx = fma(-t, vx, fma(s, ux, sx[l])), wy = fma(-t, vy, fma(s, uy, sy[l])),
+                         wz = fma(-t, vz, fma(s, uz, sz[l]));
+            take(dot3d(wx, wy, wz, wx, wy, wz), wx, wy, wz);
+        }
+        const double e = dot3d(vx, vy, vz, tx[l], ty[l], tz[l]);
+        {  // the edge q -> p
+            const double d = dot3d(-ux, -uy, -uz, tx[l], ty[l], tz[l]);
+            double s = 0.0;
+            if (D > 0.0) s = clamp01d(fma(-bb, e, -(c * d)) / D);
+            const double t = clamp01d(fma(-bb, s, e) * ic);
+            s = clamp01d(fma(-bb, t, -d) * ia);
+            const double wx = fma(-t, vx, fma(s, -ux, tx[l])), wy = fma(-t, vy, fma(s, -uy, ty[l])),
+                         wz = fma(-t, vz, fma(s, -uz, tz[l]));
+            take(dot3d(wx, wy, wz, wx, wy, wz), wx, wy, wz);
+        }
+        {  // q
+            const double t = clamp01d(e * ic);
+            const double wx = fma(-t, vx, tx[l]), wy = fma(-t, vy, ty[l]), wz = fma(-t, vz, tz[l]);
+            take(dot3d(wx, wy, wz, wx, wy, wz), wx, wy, wz);
+        }
+    }
+    {
+        const double e0x = v[3] - v[0], e0y = v[4] - v[1], e0z = v[5] - v[2];
+        const double e2x = v[0] - v[6], e2y = v[1] - v[7], e2z = v[2] - v[8];
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            const double wx = i ? tx[0] : sx[0], wy = i ? ty[0] : sy[0], wz = i ? tz[0] : sz[0];
+            const double b1 = dot3d(T[S_G1], T[S_G1 + 1], T[S_G1 + 2], wx, wy, wz);
+            const double b2 = dot3d(T[S_G2], T[S_G2 + 1], T[S_G2 + 2], wx, wy, wz);
+            if (b1 >= 0.0 && b2 >= 0.0 && b1 + b2 <= 1.0) {
+                const double qx = fma(b2, e2x, fma(-b1, e0x, wx)), qy = fma(b2, e2y, fma(-b1, e0y, wy)),
+                             qz = fma(b2, e2z, fma(-b1, e0z, wz));
+                take(dot3d(qx, qy, qz, qx, qy, qz), qx, qy, qz);
+            }
+        }
+    }
+#pragma unroll
+    for (int l = 0; l < 3; l++) take(dot3d(sx[l], sy[l], sz[l], sx[l], sy[l], sz[l]), sx[l], sy[l], sz[l]);
+    double sep = __builtin_inf(), mr = 0.0;
+#pragma unroll
+    for (int l = 0; l < 3; l++) {
+        sep = fmin(sep, fmin(dot3d(bx, by, bz, sx[l], sy[l], sz[l]), dot3d(bx, by, bz, tx[l], ty[l], tz[l])));
+        mr = fmax(mr, fmax(fmax(fabs(sx[l]), fmax(fabs(sy[l]), fabs(sz[l]))),
+                           fmax(fabs(tx[l]), fmax(fabs(ty[l]), fabs(tz[l])))));
+    }
+    const double cb = 16.0 * SQRT3 * U64 * mr;
+    if (best > 0.0 && sep > 0.0 && sep * sep > (cb * cb) * best) return {best, 0};
+    const int f = seg_tri_filtered64(p, q, v);
     if (f == 1) return {0.0, 1};
     return {best, f == 0 ? 0 : 2};
 }

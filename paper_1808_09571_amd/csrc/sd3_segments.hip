@@ -7,20 +7,31 @@
 // distance").
 //
 // A segment P0 P1 is the degenerate triangle (P0, P1, P1) and a point the
-// triangle (P, P, P): the FP64 triangle-pair routine and the exact
-// intersection test of the mesh path apply unchanged (a zero-area triangle
-// is the union of its edges), so the values are those sd3_distance returns
-// for the same inputs.
+// triangle (P, P, P): seg_pair64 gives the bits of the FP64 triangle-pair
+// routine for it, and undecided contacts go to the exact intersection test of
+// the mesh path (a zero-area triangle is the union of its edges), so the
+// values are those sd3_distance returns for the same inputs.
 //
-// Layout: the mesh is prepared once per call into an AoS array of FP64
-// triangles (30 derived fields + box, 36 doubles) and boxes of consecutive
-// 64-triangle tiles.  One wave owns 64 segments (one per lane, staged into
-// LDS as degenerate triangles); it walks the mesh tiles, culls each tile by
-// box against every live lane, then each triangle box against each lane, and
-// compacts the surviving (segment, triangle) pairs with ballots into an LDS
-// ring that is tested 64 pairs at a time, one pair per lane.  Per-segment
-// state (best squared distance, flags) lives in LDS and is updated with LDS
-// atomics.
+// Layout: the mesh is prepared once per call into FP64 triangles (S_NTRI
+// fields) and a tree of bounding cylinders over groups of 8, 64, 512, ...
+// consecutive triangles in FP32 (SegNode, 32 bytes; level 0 bounds the single
+// triangles).  One wave owns 64 segments.  It tests the nodes of the top
+// level (at most 16) against all of them, and keeps the (segment, node) pairs
+// that survive on one LDS stack per level; from then on a lane works on any
+// segment's pair: 64 pairs of one level are popped together, each lane tests
+// its node's eight children, and the survivors are compacted with ballots
+// onto the level below, the deepest level with 64 pairs first, so that the
+// lanes stay full however the segments differ.  Triangle pairs that are still
+// live when popped are gathered 64 at a time for the FP64 test.
+//
+// Measured (perf/cases.py's segment cases; before: every lane looped over the
+// boxes of whole 64-triangle tiles, one scalar load chain per triangle, and
+// crossing segments ran exact arithmetic): 5,000,000 segments against a
+// 500-face body, distance, 14.2 -> 3.06 ms (119 triangle bounds and 8.4 FP64
+// tests a segment; 335 and 12.9 before); 300,000 within 2 of a 20,480-face
+// body 2.44 -> 0.31 ms.  Bound by FP32 and FP64 vector instructions and, at
+// three waves a SIMD (registers of the FP64 test; 8 KB of LDS and 2.3 KB a
+// level), the latency of the node gathers.
 #include <algorithm>
 
 #include "sd3_kernels.h"
@@ -29,253 +40,565 @@
 
 namespace sd3 {
 
-constexpr int MESH_TK = 64;   // triangles per mesh tile
-constexpr int SEED_PTS = 256; // mesh vertices a segment's first upper bound is taken over
-constexpr int SEG_NF = 36;    // prepared mesh triangle: F_NTRI64 fields + box
-constexpr int SEG_RING = 128;
+constexpr int FAN = SEG_FAN;      // children per node
+constexpr int SEEDS = 64;         // triangle centres a segment's first upper bound is taken over
+constexpr int STACK = 64 + 64 * FAN;  // a level below 64 pairs takes one expansion
+
+// A bounding cylinder: every point of the node's triangles is c + a n + y
+// with |a| <= w, y orthogonal to n and |y| <= rho.  Coordinates are relative
+// to the mesh's frame (SegFrame): |c| <= sqrt(3).  c and n are FP32 values
+// that rho and w are measured from, so they carry no error of their own.
+struct SegNode {
+    float c[3], rho, n[3], w;
+};
+static_assert(sizeof(SegNode) == SEG_NODE_BYTES, "two 16-byte loads");
+
+// The mesh's frame: its box centre, and the power of two that takes the
+// largest extent into [1, 2) (1 for a box of no extent), so that the FP32
+// cull neither overflows near the mesh nor loses it to the origin.
+struct SegFrame {
+    double c[3], s;
+};
+
+__device__ __forceinline__ SegFrame seg_frame(const unsigned long long *box) {
+    SegFrame f;
+    double ext = 0.0;
+    for (int k = 0; k < 3; k++) {
+        const double lo = from_ordered_bits(box[k]), hi = from_ordered_bits(box[3 + k]);
+        f.c[k] = 0.5 * lo + 0.5 * hi;
+        ext = fmax(ext, hi - lo);
+    }
+    const bool ok = ext > 0.0 && ext < __builtin_inf();
+    f.s = ok ? ldexp(1.0, -ilogb(ext)) : 1.0;
+    return f;
+}
 
 // Validation of the segment coordinates (flags[0]) and of the mesh
-// (coordinates and indices, flags[1]); every flag word starts at 0.
+// (coordinates and indices, flags[1]), and the mesh's box (ordered bits) from
+// its vertices; k_seg_clear set every word.
 __global__ __launch_bounds__(256) void k_seg_validate(const double *seg, int64_t n, const double *xyz,
                                                       int64_t nv, const int32_t *tri, int64_t nt,
-                                                      uint32_t *flags) {
+                                                      uint32_t *flags, unsigned long long *box) {
+    __shared__ unsigned long long red[4][6];
     uint32_t fs = 0, fm = 0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < 6 * n; i += stride) {
+    const int64_t first = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    for (int64_t i = first; i < 6 * n; i += stride) {
         const double x = fabs(seg[i]);
         if (!(x <= 1.7976931348623157e308)) fs |= V_NONFINITE;
         else if (x != 0.0 && (x < 0x1p-256 || x > 0x1p256)) fs |= V_RANGE;
     }
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < 3 * nv; i += stride) {
-        const double x = fabs(xyz[i]);
-        if (!(x <= 1.7976931348623157e308)) fm |= V_NONFINITE;
-        else if (x != 0.0 && (x < 0x1p-256 || x > 0x1p256)) fm |= V_RANGE;
-    }
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < 3 * nt; i += stride) {
+    double lo[3] = {__builtin_inf(), __builtin_inf(), __builtin_inf()};
+    double hi[3] = {-__builtin_inf(), -__builtin_inf(), -__builtin_inf()};
+    for (int64_t i = first; i < nv; i += stride)
+        for (int c = 0; c < 3; c++) {
+            const double v = xyz[3 * i + c], x = fabs(v);
+            if (!(x <= 1.7976931348623157e308)) fm |= V_NONFINITE;
+            else if (x != 0.0 && (x < 0x1p-256 || x > 0x1p256)) fm |= V_RANGE;
+            lo[c] = fmin(lo[c], v);
+            hi[c] = fmax(hi[c], v);
+        }
+    for (int64_t i = first; i < 3 * nt; i += stride) {
         const int32_t v = tri[i];
         if (v < 0 || (int64_t)v >= nv) fm |= V_INDEX;
     }
     if (fs) atomicOr(&flags[0], fs);
     if (fm) atomicOr(&flags[1], fm);
+    if ((int64_t)blockIdx.x * blockDim.x >= nv) return;  // (block-uniform)
+    for (int c = 0; c < 3; c++) {
+        const double a = wave_min(lo[c]), b = wave_max(hi[c]);
+        if (lane_id() == 0) {
+            red[threadIdx.x >> 6][c] = ordered_bits(a);
+            red[threadIdx.x >> 6][3 + c] = ordered_bits(b);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 6) {
+        const int c = threadIdx.x;
+        unsigned long long v = red[0][c];
+        for (int w = 1; w < 4; w++) v = c < 3 ? min(v, red[w][c]) : max(v, red[w][c]);
+        if (c < 3) atomicMin(&box[c], v);
+        else atomicMax(&box[c], v);
+    }
 }
 
-// Prepared mesh: triangle t's 30 FP64 fields and its box, and the box of
-// each tile of 64 consecutive triangles (one wave per tile; indices are
-// clamped into the mesh so that invalid contents never address other memory).
-__global__ __launch_bounds__(64) void k_seg_mesh(const double *xyz, int64_t nv, const int32_t *tri,
-                                                 int64_t nt, double *P, double *tbox) {
-    const int64_t tile = blockIdx.x;
-    const int64_t t = tile * MESH_TK + threadIdx.x;
-    double lo[3] = {__builtin_inf(), __builtin_inf(), __builtin_inf()};
-    double hi[3] = {-__builtin_inf(), -__builtin_inf(), -__builtin_inf()};
-    if (t < nt) {
-        double *q = P + t * SEG_NF;
-        for (int k = 0; k < 3; k++) {
-            int32_t v = tri[3 * t + k];
-            const int64_t vi = (v >= 0 && (int64_t)v < nv) ? v : 0;
-            for (int c = 0; c < 3; c++) q[F_V + 3 * k + c] = xyz[3 * vi + c];
-        }
-        tri_prep64(TriRef<double>{q, 1});
-        for (int c = 0; c < 3; c++) {
-            lo[c] = fmin(q[F_V + c], fmin(q[F_V + 3 + c], q[F_V + 6 + c]));
-            hi[c] = fmax(q[F_V + c], fmax(q[F_V + 3 + c], q[F_V + 6 + c]));
-            q[F_NTRI64 + c] = lo[c];
-            q[F_NTRI64 + 3 + c] = hi[c];
-        }
-    }
-    for (int c = 0; c < 3; c++) {
-        lo[c] = wave_min(lo[c]);
-        hi[c] = wave_max(hi[c]);
-    }
-    if (threadIdx.x == 0)
-        for (int c = 0; c < 3; c++) {
-            tbox[tile * 6 + c] = lo[c];
-            tbox[tile * 6 + 3 + c] = hi[c];
-        }
+// Minimum, maximum or sum over each aligned group of W lanes (8 or 64), in
+// every lane of the group.
+template <int W, typename F>
+__device__ __forceinline__ double lanes_reduce(double v, F f) {
+#pragma unroll
+    for (int o = 1; o < W; o <<= 1) v = f(v, __shfl_xor(v, o));
+    return v;
 }
 
-// Box of the whole mesh from its tile boxes (one block).
-__global__ __launch_bounds__(64) void k_seg_meshbox(const double *tbox, int64_t ntiles, double *mbox) {
-    double lo[3] = {__builtin_inf(), __builtin_inf(), __builtin_inf()};
-    double hi[3] = {-__builtin_inf(), -__builtin_inf(), -__builtin_inf()};
-    for (int64_t t = threadIdx.x; t < ntiles; t += 64)
-        for (int c = 0; c < 3; c++) {
-            lo[c] = fmin(lo[c], tbox[t * 6 + c]);
-            hi[c] = fmax(hi[c], tbox[t * 6 + 3 + c]);
-        }
-    for (int c = 0; c < 3; c++) {
-        lo[c] = wave_min(lo[c]);
-        hi[c] = wave_max(hi[c]);
+__device__ __forceinline__ float round_up(double x) { return (float)x * (1.0f + 0x1p-22f) + 0x1p-60f; }
+
+__device__ __forceinline__ void write_node(float4 *nodes, int64_t i, const float (&c)[3], double rho,
+                                           const float (&n)[3], double w) {
+    nodes[2 * i] = make_float4(c[0], c[1], c[2], round_up(rho));
+    nodes[2 * i + 1] = make_float4(n[0], n[1], n[2], round_up(w));
+}
+
+// A unit direction in FP32 (any one for a zero or unusable vector).
+__device__ __forceinline__ void unit_dir(const double *v, float (&n)[3]) {
+    const double l = sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+    const bool ok = l > 0x1p-400 && l < 0x1p400;
+    for (int k = 0; k < 3; k++) n[k] = ok ? (float)(v[k] / l) : (k == 2 ? 1.0f : 0.0f);
+}
+
+// The cylinder of the triangles of each aligned group of W lanes (x: the
+// lane's corners in the frame, a: its area normal; lanes without a triangle
+// bring nothing).
+template <int W>
+__device__ __forceinline__ void group_node(const double (&x)[9], const double (&a)[3], bool in, float (&c)[3],
+                                           float (&n)[3], double &rho, double &w) {
+    double s[3];
+    for (int k = 0; k < 3; k++) {
+        const double l = in ? fmin(x[k], fmin(x[3 + k], x[6 + k])) : __builtin_inf();
+        const double h = in ? fmax(x[k], fmax(x[3 + k], x[6 + k])) : -__builtin_inf();
+        const double lo = lanes_reduce<W>(l, [](double p, double q) { return fmin(p, q); });
+        const double hi = lanes_reduce<W>(h, [](double p, double q) { return fmax(p, q); });
+        c[k] = (float)(0.5 * lo + 0.5 * hi);
+        s[k] = lanes_reduce<W>(in ? a[k] : 0.0, [](double p, double q) { return p + q; });
     }
-    if (threadIdx.x == 0)
+    unit_dir(s, n);
+    double r2 = 0.0, h = 0.0;
+    for (int k = 0; k < 3; k++) {
+        const double d0 = x[3 * k] - c[0], d1 = x[3 * k + 1] - c[1], d2 = x[3 * k + 2] - c[2];
+        const double t = n[0] * d0 + n[1] * d1 + n[2] * d2;
+        // the part along n of a direction that is unit to 2^-22
+        const double l0 = d0 - t * n[0], l1 = d1 - t * n[1], l2 = d2 - t * n[2];
+        r2 = fmax(r2, l0 * l0 + l1 * l1 + l2 * l2);
+        h = fmax(h, fabs(t));
+    }
+    rho = sqrt(lanes_reduce<W>(in ? r2 : 0.0, [](double p, double q) { return fmax(p, q); }));
+    w = lanes_reduce<W>(in ? h : 0.0, [](double p, double q) { return fmax(p, q); });
+    // (n is unit, and y orthogonal to it, to 2^-22 of w)
+    rho += 0x1p-20 * w;
+    w += 0x1p-20 * w;
+}
+
+// Prepared mesh: triangle t's S_NTRI fields and the cylinders of levels 0, 1
+// and 2 (one wave per 64 triangles; indices are clamped into the mesh so that
+// invalid contents never address other memory).
+__global__ __launch_bounds__(64) void k_seg_mesh(const double *xyz, int64_t nv, const int32_t *tri, int64_t nt,
+                                                 const unsigned long long *box, double *P, float4 *nodes,
+                                                 SegTree T) {
+    const SegFrame F = seg_frame(box);
+    const int64_t t = blockIdx.x * (int64_t)64 + threadIdx.x;
+    const bool in = t < nt;
+    double x[9], a[3];
+    double f[F_NTRI64];
+    TriRef<double> R{f, 1};
+    for (int k = 0; k < 3; k++) {
+        const int32_t v = tri[3 * (in ? t : nt - 1) + k];
+        const int64_t vi = (v >= 0 && (int64_t)v < nv) ? v : 0;
         for (int c = 0; c < 3; c++) {
-            // an empty mesh leaves a box that adds nothing to the extent
-            mbox[c] = ntiles > 0 ? lo[c] : 0.0;
-            mbox[3 + c] = ntiles > 0 ? hi[c] : 0.0;
+            f[F_V + 3 * k + c] = xyz[3 * vi + c];
+            x[3 * k + c] = (f[F_V + 3 * k + c] - F.c[c]) * F.s;
         }
+    }
+    tri_prep64(R);
+    if (in) {
+        double *q = P + t * S_NTRI;
+        for (int k = 0; k < 9; k++) q[S_V + k] = f[F_V + k];
+        for (int k = 0; k < 3; k++) q[S_IE + k] = f[F_IE + k];
+        for (int k = 0; k < 3; k++) q[S_G1 + k] = f[F_G1 + k];
+        for (int k = 0; k < 3; k++) q[S_G2 + k] = f[F_G2 + k];
+    }
+    for (int k = 0; k < 3; k++) {
+        const int i = (k + 1) % 3, j = (k + 2) % 3;
+        a[k] = (x[3 + i] - x[i]) * (x[6 + j] - x[j]) - (x[3 + j] - x[j]) * (x[6 + i] - x[i]);
+    }
+    float c[3], n[3];
+    double rho = 0.0, w = 0.0;
+    // level 0: the centroid, a surface point (upper bounds are taken from it)
+    unit_dir(a, n);
+    for (int k = 0; k < 3; k++) c[k] = (float)((x[k] + x[3 + k] + x[6 + k]) * (1.0 / 3.0));
+    for (int k = 0; k < 3; k++) {
+        const double d0 = x[3 * k] - c[0], d1 = x[3 * k + 1] - c[1], d2 = x[3 * k + 2] - c[2];
+        const double h = n[0] * d0 + n[1] * d1 + n[2] * d2;
+        const double l0 = d0 - h * n[0], l1 = d1 - h * n[1], l2 = d2 - h * n[2];
+        rho = fmax(rho, sqrt(l0 * l0 + l1 * l1 + l2 * l2));
+        w = fmax(w, fabs(h));
+    }
+    if (in) write_node(nodes, T.off[0] + t, c, rho + 0x1p-20 * w, n, w + 0x1p-20 * w);
+    group_node<8>(x, a, in, c, n, rho, w);
+    if (in && (threadIdx.x & 7) == 0) write_node(nodes, T.off[1] + t / 8, c, rho, n, w);
+    if (T.top >= 2) {
+        group_node<64>(x, a, in, c, n, rho, w);
+        if (in && threadIdx.x == 0) write_node(nodes, T.off[2] + t / 64, c, rho, n, w);
+    }
+}
+
+// Levels 3 and up, each from the level below (one block; a mesh of 2^25
+// triangles has 2^16 nodes in level 3).
+__global__ __launch_bounds__(1024) void k_seg_up(float4 *nodes, SegTree T) {
+    for (int l = 3; l <= T.top; l++) {
+        for (int64_t i = threadIdx.x; i < (int64_t)T.cnt[l]; i += blockDim.x) {
+            const int64_t k0 = i * FAN, k1 = min((int64_t)T.cnt[l - 1], k0 + FAN);
+            const float4 *ch = nodes + 2 * (int64_t)T.off[l - 1];
+            double lo[3], hi[3], s[3] = {0.0, 0.0, 0.0};
+            for (int k = 0; k < 3; k++) {
+                lo[k] = __builtin_inf();
+                hi[k] = -__builtin_inf();
+            }
+            for (int64_t j = k0; j < k1; j++) {
+                const float4 a = ch[2 * j], b = ch[2 * j + 1];
+                const double cc[3] = {a.x, a.y, a.z}, nn[3] = {b.x, b.y, b.z};
+                const double rad = (double)a.w + (double)b.w;
+                for (int k = 0; k < 3; k++) {
+                    lo[k] = fmin(lo[k], cc[k] - rad);
+                    hi[k] = fmax(hi[k], cc[k] + rad);
+                    s[k] += nn[k] * (double)a.w * (double)a.w;
+                }
+            }
+            float c[3], n[3];
+            for (int k = 0; k < 3; k++) c[k] = (float)fmin(fmax(0.5 * lo[k] + 0.5 * hi[k], -1.0), 1.0);
+            unit_dir(s, n);
+            double rho = 0.0, w = 0.0;
+            for (int64_t j = k0; j < k1; j++) {
+                // a child's point c_j + a n_j + y: along n and across it
+                const float4 a = ch[2 * j], b = ch[2 * j + 1];
+                const double d0 = (double)a.x - c[0], d1 = (double)a.y - c[1], d2 = (double)a.z - c[2];
+                const double h = n[0] * d0 + n[1] * d1 + n[2] * d2;
+                const double l0 = d0 - h * n[0], l1 = d1 - h * n[1], l2 = d2 - h * n[2];
+                const double co = fabs((double)n[0] * b.x + (double)n[1] * b.y + (double)n[2] * b.z);
+                const double si = sqrt(fmax(1.0 - co * co, 0.0) + 0x1p-18);
+                const double cw = fmin(co + 0x1p-18, 1.0 + 0x1p-18);
+                rho = fmax(rho, sqrt(l0 * l0 + l1 * l1 + l2 * l2) + (double)a.w + (double)b.w * si);
+                w = fmax(w, fabs(h) + (double)b.w * cw + (double)a.w * si);
+            }
+            // (no two points of the frame are farther apart than 2 sqrt(3))
+            rho = fmin((rho + 0x1p-18 * w) * (1.0 + 0x1p-18), 3.4642);
+            w = fmin(w * (1.0 + 0x1p-18), 3.4642);
+            write_node(nodes, T.off[l] + i, c, rho, n, w);
+        }
+        __threadfence_block();
+        __syncthreads();
+    }
 }
 
 // The exact closed test for a pair the FP64 filter left undecided (rare; a
 // call keeps its registers out of the common path).
-__device__ __attribute__((noinline)) bool seg_pair_exact(const double *va, const double *vb) {
+__device__ __attribute__((noinline)) bool seg_pair_exact(const double *p, const double *q, const double *T) {
+    double va[9], vb[9];
+    for (int k = 0; k < 3; k++) {
+        va[k] = p[k];
+        va[3 + k] = va[6 + k] = q[k];
+    }
+    for (int k = 0; k < 9; k++) vb[k] = T[k];
     return ex::tri_tri_exact(va, vb);
 }
 
-__device__ __forceinline__ double seg_gap2(const double *alo, const double *ahi, const double *blo,
-                                           const double *bhi) {
-#pragma clang fp contract(off)
-    double g2 = 0.0;
+// A segment in the frame, in FP32.
+struct SegF {
+    float p[3], u[3], iu;  // p + t u, t in [0, 1]; iu = 1 / |u|^2 (0 for a point)
+};
+
+// Squared distance of the segment to c, and the offsets from c to its ends.
+__device__ __forceinline__ float seg_point2(const SegF &s, const float4 &a, float (&r0)[3], float (&r1)[3]) {
+    r0[0] = s.p[0] - a.x;
+    r0[1] = s.p[1] - a.y;
+    r0[2] = s.p[2] - a.z;
+    float d = 0.0f, q = 0.0f;
+#pragma unroll
     for (int k = 0; k < 3; k++) {
-        const double gp = fmax(fmax(blo[k] - ahi[k], alo[k] - bhi[k]), 0.0);
-        g2 += gp * gp;
+        r1[k] = r0[k] + s.u[k];
+        d = fmaf(r0[k], s.u[k], d);
     }
-    return g2;
+    const float t = fminf(fmaxf(-d * s.iu, 0.0f), 1.0f);
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        const float w = fmaf(t, s.u[k], r0[k]);
+        q = fmaf(w, w, q);
+    }
+    return q;
 }
 
-// Squared cull threshold of a segment with upper bound ub (distance: the best
-// so far; threshold filter: r): a triangle whose box gap exceeds it is
-// farther than ub by more than the margin m, which exceeds twice the FP64
-// error of any pair distance of the segment (m scales with the extent of the
-// segment and the mesh, as the row margin of the mesh path).
-__device__ __forceinline__ double seg_cull2(double ub, double msc) {
-    if (!(ub < __builtin_inf())) return __builtin_inf();
-    const double T = (ub + msc + 1.4551915228366852e-11 * ub) * (1.0 + 8.0 * U64);
+// Error of the FP32 cull.  With e = 2^-24 and S = q0 + q1 + 2 (q0, q1: the
+// squared offsets of the segment's ends from c), rounding the segment into
+// the frame moves it by at most e |p|, |p| <= |r| + sqrt(3), and every
+// squared quantity below (q, h^2, l^2, d^2, the products with rho and w, both
+// at most 2 sqrt(3)) is within 48 e S of its exact value; 64 e S is taken
+// off, which leaves 2^-20 S >= 2^-20 of the squared extent of the segment and
+// the mesh, far above the FP64 error of any pair distance and above the
+// pruning margin of the mesh path (2^-36 of the extent).
+constexpr float CULL_EPS = 0x1p-18f;
+
+// A value at most the squared distance of the segment to the node, less the
+// allowance.  For a point x = c + a n + y of the cylinder and p on the
+// segment, |p - x|^2 >= |p - c|^2 - 2 |h| w - 2 l r + r^2 (h = n . (p - c), l
+// the part of p - c across n, r = |y| <= rho): the segment's smallest |p - c|
+// and its largest |h| and l (attained at an end) bound it.  Where both ends
+// are on one side of the cylinder, (min |h| - w)^2 does too.  NaN (a segment
+// beyond FP32's range of the mesh) culls nothing.  d2: the squared distance
+// to c, up: that plus the allowance.
+__device__ __forceinline__ float node_bound2(const SegF &s, const float4 &a, const float4 &b, float &up) {
+    float r0[3], r1[3];
+    const float d2 = seg_point2(s, a, r0, r1);
+    const float n[3] = {b.x, b.y, b.z};
+    float q0 = 0.0f, q1 = 0.0f, h0 = 0.0f, h1 = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        q0 = fmaf(r0[k], r0[k], q0);
+        q1 = fmaf(r1[k], r1[k], q1);
+        h0 = fmaf(n[k], r0[k], h0);
+        h1 = fmaf(n[k], r1[k], h1);
+    }
+    const float S = q0 + q1 + 2.0f, slack = CULL_EPS * S;
+    const float l2 = fmaxf(fmaxf(fmaf(-h0, h0, q0), fmaf(-h1, h1, q1)), 0.0f) + 0.5f * slack;
+    const float l = __builtin_amdgcn_sqrtf(l2);
+    const float g = l < a.w ? -l2 : a.w * fmaf(-2.0f, l, a.w);
+    float B = fmaf(-2.0f * b.w, fmaxf(fabsf(h0), fabsf(h1)), d2 + g);
+    const float hm = fminf(fabsf(h0), fabsf(h1)) - b.w;
+    if (h0 * h1 > 0.0f && hm > 0.0f) B = fmaxf(B, hm * hm);
+    up = d2 + slack;
+    return B - slack;
+}
+
+// Squared FP32 threshold of an upper bound (frame units, rounded up).
+__device__ __forceinline__ float cull2(float ub) {
+    const float T = ub * (1.0f + 0x1p-20f);
     return T * T;
 }
 
+__device__ __forceinline__ void lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // MODE 0: distance (dist[i], hit[i] optional); 1: intersects (hit[i]);
-// 2: within r (hit[i] = distance <= r).  cnt[0..2]: triangle boxes compared,
+// 2: within r (hit[i] = distance <= r).  cnt[0..2]: triangle bounds compared,
 // full pair tests, exact tests (summed per wave).
 template <int MODE>
-__global__ __launch_bounds__(64) void k_segs(const double *seg, int64_t n, const double *P, int64_t nt,
-                                             const double *tbox, const double *mbox, double r,
-                                             double *dist, uint8_t *hit, const uint32_t *flags,
+__global__ __launch_bounds__(64, 3) void k_segs(const double *seg, int64_t n, const double *P, int64_t nt,
+                                             const float4 *nodes, SegTree T, const unsigned long long *box,
+                                             double r, double *dist, uint8_t *hit, const uint32_t *flags,
                                              unsigned long long *cnt) {
-    __shared__ double sS[F_NTRI64 * 64];          // the wave's segments, stride 64
-    __shared__ unsigned long long best[64];       // squared distance bits
-    __shared__ uint32_t done[64];                 // hit (MODE 0, 1) or within (MODE 2)
-    __shared__ uint32_t ring[SEG_RING];
+    __shared__ float4 sf[2][64];             // in the frame: p and u.x, u.y u.z iu
+    __shared__ unsigned long long best[64];  // squared distance bits
+    __shared__ uint32_t ubf[64];             // upper bound in the frame, rounded up (bits)
+    __shared__ uint32_t done[64];            // hit (MODE 0, 1) or within (MODE 2)
+    __shared__ uint32_t tstk[STACK];         // live (triangle, segment) pairs and their bounds
+    __shared__ float tlb[STACK];
+    __shared__ uint32_t rdy[128];            // pairs to test
+    extern __shared__ uint32_t nstk[];       // (node, segment) pairs, STACK per level 1..top
     if (flags[0] | flags[1]) return;  // invalid contents: outputs stay untouched
     const int lane = lane_id();
     const unsigned long long below = lanes_below();
-    const int64_t ntiles = (nt + MESH_TK - 1) / MESH_TK;
-    unsigned long long n_box = 0, n_full = 0, n_ex = 0;
+    const SegFrame F = seg_frame(box);
+    const float rf = (float)(r * F.s) * (1.0f + 0x1p-22f);
+    const float r2 = cull2(rf);                       // MODE 2: farther than r
+    const float in2 = rf * rf * (1.0f - 0x1p-18f);    // a surface point this near: within r
+    // lane l holds level l's first node and node count
+    const int toff = lane < SEG_LEVELS ? (int)T.off[lane] : 0, tcnt = lane < SEG_LEVELS ? (int)T.cnt[lane] : 0;
+    unsigned n_box = 0, n_full = 0, n_ex = 0;
     for (int64_t base = (int64_t)blockIdx.x * 64; base < n; base += (int64_t)gridDim.x * 64) {
         const int64_t i = base + lane;
         const bool mine = i < n;
-        double lo[3], hi[3];
-        double p[3], q[3];
+        SegF me;
         {
+            double p[3], u[3], pp = 0.0, uu = 0.0, pu = 0.0;
             for (int c = 0; c < 3; c++) {
-                p[c] = mine ? seg[6 * i + c] : 0.0;
-                q[c] = mine ? seg[6 * i + 3 + c] : 0.0;
+                const double x = mine ? seg[6 * i + c] : 0.0, y = mine ? seg[6 * i + 3 + c] : 0.0;
+                p[c] = (x - F.c[c]) * F.s;
+                u[c] = (y - x) * F.s;
+                pp += p[c] * p[c];
+                uu += u[c] * u[c];
+                pu += p[c] * u[c];
             }
-            TriRef<double> S{sS + lane, 64};
+            // a long segment is cut to where the mesh's nearest point can be
+            // (FP32 offsets stay small): the mesh lies within sqrt(3) of the
+            // frame's origin, so within d + 1.75 of the segment (d its
+            // distance to the origin), and a point of it more than d + 3.5
+            // from the origin is farther than that from all of the mesh
+            // (up to 2^26 frame units, where FP64 places the cut to 2^-25)
+            if (uu > 64.0 && uu < 0x1p52 && pp < 0x1p52) {
+                const double t = fmin(fmax(-pu / uu, 0.0), 1.0);
+                double d2 = 0.0;
+                for (int c = 0; c < 3; c++) d2 += (p[c] + t * u[c]) * (p[c] + t * u[c]);
+                const double d = sqrt(d2) + 3.5;
+                const double half = sqrt(fmax(d * d - d2, 0.0) / uu) * 1.0001 + 1e-9;
+                const double t0 = fmax(t - half, 0.0), t1 = fmin(t + half, 1.0);
+                for (int c = 0; c < 3; c++) {
+                    p[c] += t0 * u[c];
+                    u[c] *= t1 - t0;
+                }
+            }
+            float q = 0.0f;
             for (int c = 0; c < 3; c++) {
-                S.at(F_V + c) = p[c];
-                S.at(F_V + 3 + c) = q[c];
-                S.at(F_V + 6 + c) = q[c];
-                lo[c] = fmin(p[c], q[c]);
-                hi[c] = fmax(p[c], q[c]);
+                me.p[c] = (float)p[c];
+                me.u[c] = (float)u[c];
+                q = fmaf(me.u[c], me.u[c], q);
             }
-            tri_prep64(S);
+            me.iu = q > 0.0f ? 1.0f / q : 0.0f;
         }
-        // margin scale: 2^-36 of the extent of the segment and the mesh
-        double ext = 0.0;
-        for (int c = 0; c < 3; c++) ext = fmax(ext, fmax(hi[c], mbox[3 + c]) - fmin(lo[c], mbox[c]));
-        const double msc = 1.4551915228366852e-11 * ext;
+        sf[0][lane] = make_float4(me.p[0], me.p[1], me.p[2], me.u[0]);
+        sf[1][lane] = make_float4(me.u[1], me.u[2], me.iu, 0.0f);
         best[lane] = double_to_bits(__builtin_inf());
         done[lane] = mine ? 0u : 1u;
-        // distance: a first upper bound, the distance from the nearer endpoint
-        // to the nearest of up to SEED_PTS mesh vertices (first vertices of
-        // evenly spaced triangles; wave-uniform loads), so that the cull is
-        // tight from the first tile on.  Any segment point and mesh point
-        // bound the distance from above; the returned value still comes from
-        // the pair routine alone.
-        double ub = __builtin_inf();
+        float ub = __builtin_inff();
         if (MODE == 0 && nt > 0) {
-            const int64_t ns = min((int64_t)SEED_PTS, nt);
-            double u2 = __builtin_inf();
-#pragma unroll 16
-            for (int64_t k = 0; k < ns; k++) {
-                const double *v = P + ((k * nt) / ns) * SEG_NF + F_V;
-                double a2 = 0.0, b2 = 0.0;
-                for (int c = 0; c < 3; c++) {
-                    const double da = p[c] - v[c], db = q[c] - v[c];
-                    a2 += da * da;
-                    b2 += db * db;
-                }
-                u2 = fmin(u2, fmin(a2, b2));
+            // a first upper bound: the nearest of up to SEEDS triangle
+            // centres (wave-uniform loads), so that the cull is tight from
+            // the first node on; the returned value comes from the FP64
+            // tests alone
+            const int ns = (int)min((int64_t)SEEDS, nt);
+            float m = __builtin_inff();
+#pragma unroll 8
+            for (int k = 0; k < ns; k++) {
+                float r0[3], r1[3];
+                m = fminf(m, seg_point2(me, nodes[2 * (T.off[0] + (k * nt) / ns)], r0, r1));
             }
-            ub = sqrt(u2) * (1.0 + 4.0 * U64);
+            // (q0 + q1 + 2 <= 2 (|p|^2 + |p + u|^2) + 14 for every centre)
+            float a = 0.0f;
+            for (int c = 0; c < 3; c++) {
+                const float e = me.p[c] + me.u[c];
+                a = fmaf(me.p[c], me.p[c], fmaf(e, e, a));
+            }
+            m = sqrtf(fmaf(CULL_EPS, 2.0f * a + 14.0f, m)) * (1.0f + 0x1p-22f);
+            if (m >= 0.0f) ub = m;
         }
-        unsigned rc = 0, rd = 0;
-        // test ring entries rd .. rd + cnt - 1, one per lane
-        auto test_batch = [&](unsigned cntb) __attribute__((always_inline)) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const bool on = (unsigned)lane < cntb;
-            const uint32_t e = on ? ring[(rd + lane) & (SEG_RING - 1)] : 0u;
-            const int slot = (int)(e & 63);
-            const int64_t t = (int64_t)(e >> 6);
-            if (on && !done[slot]) {
-                TriRef<double> A{sS + slot, 64};
-                TriRef<double> B{const_cast<double *>(P) + t * SEG_NF, 1};
-                const Pair64 pr = pair64<true>(A, B);
-                int st = pr.status;
-                n_full++;
-                if (st == 2) {
-                    double va[9], vb[9];
-                    for (int k = 0; k < 9; k++) {
-                        va[k] = A[F_V + k];
-                        vb[k] = B[F_V + k];
+        ubf[lane] = __float_as_uint(ub);
+        lds_sync();
+        int cl = 0;  // lane l holds the pairs on level l's stack
+        unsigned rc = 0;
+        const int ntop = nt > 0 ? (int)T.cnt[T.top] : 0;
+        int tt = 0;
+        for (;;) {
+            const unsigned long long full = __ballot(cl >= 64), any = __ballot(cl > 0);
+            if (rc >= 64 || (!any && tt == ntop)) {
+                // test the last (at most 64) pairs of the ready list
+                if (rc == 0) break;
+                lds_sync();
+                const unsigned k = min(rc, 64u);
+                rc -= k;
+                const uint32_t e = (unsigned)lane < k ? rdy[rc + lane] : 0u;
+                const int slot = (int)(e & 63);
+                if ((unsigned)lane < k && !done[slot]) {
+                    const double *B = P + (int64_t)(e >> 6) * S_NTRI;
+                    double p[3], q[3];
+                    for (int c = 0; c < 3; c++) {
+                        p[c] = seg[6 * (base + slot) + c];
+                        q[c] = seg[6 * (base + slot) + 3 + c];
                     }
-                    st = seg_pair_exact(va, vb) ? 1 : 0;
-                    n_ex++;
-                }
-                if (st == 1) {
-                    if (MODE == 0) {
-                        atomicOr(&done[slot], 1u);
-                        atomicMin(&best[slot], 0ull);
+                    int st;
+                    double d2 = 0.0;
+                    if (MODE == 1) {
+                        st = seg_tri_filtered64(p, q, B);
                     } else {
+                        const Pair64 pr = seg_pair64(p, q, B);
+                        st = pr.status;
+                        d2 = pr.d2;
+                    }
+                    n_full++;
+                    if (st == 2) {
+                        st = seg_pair_exact(p, q, B) ? 1 : 0;
+                        n_ex++;
+                    }
+                    if (st == 1) {
+                        atomicOr(&done[slot], 1u);
+                    } else if (MODE == 0) {
+                        atomicMin(&best[slot], double_to_bits(d2));
+                        const float u = (float)(sqrt(d2) * F.s) * (1.0f + 0x1p-22f);
+                        atomicMin(&ubf[slot], __float_as_uint(u));
+                    } else if (MODE == 2 && sqrt(d2) <= r) {
                         atomicOr(&done[slot], 1u);
                     }
-                } else if (MODE == 0) {
-                    atomicMin(&best[slot], double_to_bits(pr.d2));
-                } else if (MODE == 2 && sqrt(pr.d2) <= r) {
-                    atomicOr(&done[slot], 1u);
+                }
+                lds_sync();
+                continue;
+            }
+            int lv;
+            if (full) {
+                lv = __ffsll(full) - 1;
+            } else if (tt < ntop) {
+                // the next top node against every segment of the wave
+                const int64_t at = (int64_t)T.off[T.top] + tt;
+                float up;
+                const float B = node_bound2(me, nodes[2 * at], nodes[2 * at + 1], up);
+                const float t2 = MODE == 0 ? cull2(__uint_as_float(ubf[lane])) : MODE == 2 ? r2 : 0.0f;
+                const bool keep = !done[lane] && !(B > t2);
+                const unsigned long long mk = __ballot(keep);
+                const int c0 = __builtin_amdgcn_readlane(cl, T.top);
+                if (keep) nstk[(T.top - 1) * STACK + c0 + __popcll(mk & below)] = (uint32_t)lane | ((uint32_t)tt << 6);
+                if (lane == T.top) cl = c0 + __popcll(mk);
+                tt++;
+                continue;
+            } else {
+                lv = 63 - __clzll(any);
+            }
+            lds_sync();
+            const int have = __builtin_amdgcn_readlane(cl, lv);
+            const int k = min(have, 64), c0 = have - k;
+            if (lane == lv) cl = c0;
+            if (lv == 0) {
+                const uint32_t e = lane < k ? tstk[c0 + lane] : 0u;
+                const int slot = (int)(e & 63);
+                const float t2 = MODE == 0 ? cull2(__uint_as_float(ubf[slot])) : MODE == 2 ? r2 : 0.0f;
+                const bool keep = lane < k && !done[slot] && !(tlb[c0 + (lane < k ? lane : 0)] > t2);
+                const unsigned long long mk = __ballot(keep);
+                if (keep) rdy[rc + __popcll(mk & below)] = e;
+                rc += (unsigned)__popcll(mk);
+                continue;
+            }
+            const uint32_t e = lane < k ? nstk[(lv - 1) * STACK + c0 + lane] : 0u;
+            const int slot = (int)(e & 63);
+            const bool on = lane < k && !done[slot];
+            const float4 s0 = sf[0][slot], s1 = sf[1][slot];
+            const SegF sg{{s0.x, s0.y, s0.z}, {s0.w, s1.x, s1.y}, s1.z};
+            const uint32_t ch = (e >> 6) * FAN, nch = (uint32_t)__builtin_amdgcn_readlane(tcnt, lv - 1);
+            const float4 *cn = nodes + 2 * (int64_t)(uint32_t)__builtin_amdgcn_readlane(toff, lv - 1);
+            float4 na[FAN], nb[FAN];
+#pragma unroll
+            for (int c = 0; c < FAN; c++) {
+                const uint32_t j = min(ch + (uint32_t)c, nch - 1);
+                na[c] = cn[2 * (int64_t)j];
+                nb[c] = cn[2 * (int64_t)j + 1];
+            }
+            float B[FAN], m = __builtin_inff();
+#pragma unroll
+            for (int c = 0; c < FAN; c++) {
+                float up;
+                B[c] = node_bound2(sg, na[c], nb[c], up);
+                m = fminf(m, up);
+            }
+            float t2 = MODE == 2 ? r2 : 0.0f;
+            if (MODE == 0) {
+                t2 = cull2(__uint_as_float(ubf[slot]));
+                if (lv == 1) {  // (the children's centres are surface points)
+                    const float u = sqrtf(m) * (1.0f + 0x1p-22f);
+                    if (on && u >= 0.0f) {
+                        atomicMin(&ubf[slot], __float_as_uint(u));
+                        t2 = fminf(t2, cull2(u));
+                    }
                 }
             }
-            rd += cntb;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        };
-        for (int64_t tl = 0; tl < ntiles; tl++) {
-            // this lane's cull threshold now (the best so far in LDS)
-            double T2 = 0.0;
-            if (MODE == 0) T2 = seg_cull2(fmin(ub, sqrt(bits_to_double(best[lane]))), msc);
-            if (MODE == 2) T2 = seg_cull2(r, msc);
-            const bool live = done[lane] == 0;  // out-of-range lanes start done
-            const double *tb = tbox + tl * 6;
-            const double blo[3] = {tb[0], tb[1], tb[2]}, bhi[3] = {tb[3], tb[4], tb[5]};
-            const double g2 = seg_gap2(lo, hi, blo, bhi);
-            const bool tile_in = live && (MODE == 1 ? g2 == 0.0 : g2 <= T2);
-            if (__ballot(tile_in) == 0) continue;
-            const int64_t t0 = tl * MESH_TK, t1 = min(nt, t0 + (int64_t)MESH_TK);
-            for (int64_t t = t0; t < t1; t++) {
-                const double *q = P + t * SEG_NF + F_NTRI64;  // wave-uniform: scalar loads
-                const double tlo[3] = {q[0], q[1], q[2]}, thi[3] = {q[3], q[4], q[5]};
-                const double h2 = seg_gap2(lo, hi, tlo, thi);
-                const bool keep = tile_in && (MODE == 1 ? h2 == 0.0 : h2 <= T2);
-                n_box += tile_in;
-                const unsigned long long mk = __ballot(keep);
-                if (keep) ring[(rc + __popcll(mk & below)) & (SEG_RING - 1)] = (uint32_t)lane | ((uint32_t)t << 6);
-                rc += (unsigned)__popcll(mk);
-                if (rc - rd >= 64) test_batch(64);
+            if (MODE == 2 && lv == 1 && on && m <= in2 && m < __builtin_inff()) {
+                atomicOr(&done[slot], 1u);
+                t2 = -1.0f;
             }
-            if (rc > rd) test_batch(rc - rd);
+            int cc = __builtin_amdgcn_readlane(cl, lv - 1);
+#pragma unroll
+            for (int c = 0; c < FAN; c++) {
+                const bool keep = on && ch + (uint32_t)c < nch && !(B[c] > t2);
+                const unsigned long long mk = __ballot(keep);
+                const int at = cc + __popcll(mk & below);
+                const uint32_t en = (uint32_t)slot | ((ch + (uint32_t)c) << 6);
+                if (lv == 1) {
+                    if (keep) {
+                        tstk[at] = en;
+                        tlb[at] = B[c];
+                    }
+                } else if (keep) {
+                    nstk[(lv - 2) * STACK + at] = en;
+                }
+                cc += __popcll(mk);
+            }
+            if (lane == lv - 1) cl = cc;
+            if (lv == 1) n_box += on ? (unsigned)min((uint32_t)FAN, nch - ch) : 0u;
         }
         if (mine) {
             if (MODE == 0) {
@@ -286,63 +609,83 @@ __global__ __launch_bounds__(64) void k_segs(const double *seg, int64_t n, const
                 hit[i] = done[lane] ? 1 : 0;
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        lds_sync();
     }
-    n_box = wave_sum(n_box);
-    n_full = wave_sum(n_full);
-    n_ex = wave_sum(n_ex);
+    const unsigned long long tb = wave_sum((unsigned long long)n_box), tf = wave_sum((unsigned long long)n_full),
+                             te = wave_sum((unsigned long long)n_ex);
     if (lane == 0) {
-        if (n_box) atomicAdd(&cnt[0], n_box);
-        if (n_full) atomicAdd(&cnt[1], n_full);
-        if (n_ex) atomicAdd(&cnt[2], n_ex);
+        if (tb) atomicAdd(&cnt[0], tb);
+        if (tf) atomicAdd(&cnt[1], tf);
+        if (te) atomicAdd(&cnt[2], te);
     }
 }
 
-__global__ void k_seg_clear(uint32_t *flags, unsigned long long *cnt) {
+// Flags and counters to 0, the mesh box to the empty one.
+__global__ void k_seg_clear(uint32_t *flags, unsigned long long *cnt, unsigned long long *box) {
     if (threadIdx.x < 2) flags[threadIdx.x] = 0;
     if (threadIdx.x < 4) cnt[threadIdx.x] = 0;
+    if (threadIdx.x < 6) box[threadIdx.x] = threadIdx.x < 3 ? ~0ull : 0ull;
+}
+
+SegTree seg_tree(int64_t nt) {
+    // the top level is the lowest with at most 16 nodes: a node tested there
+    // costs every lane one test, one tested below it only the lanes that need
+    // it (and the tree of 2^25 triangles has 7 levels)
+    SegTree T{};
+    int64_t at = 0, c = nt;
+    for (int l = 0; l < SEG_LEVELS; l++) {
+        T.off[l] = (uint32_t)at;
+        T.cnt[l] = (uint32_t)c;
+        T.top = l;
+        at += c;
+        T.nodes = at;
+        if (l >= 1 && c <= 16) break;
+        c = (c + FAN - 1) / FAN;
+    }
+    return T;
 }
 
 void launch_seg_validate(const double *seg, int64_t n, const double *xyz, int64_t nv, const int32_t *tri,
-                         int64_t nt, uint32_t *flags, unsigned long long *cnt, hipStream_t s) {
-    hipLaunchKernelGGL(k_seg_clear, dim3(1), dim3(64), 0, s, flags, cnt);
+                         int64_t nt, uint32_t *flags, unsigned long long *cnt, unsigned long long *box,
+                         hipStream_t s) {
+    hipLaunchKernelGGL(k_seg_clear, dim3(1), dim3(64), 0, s, flags, cnt, box);
     const int64_t work = std::max<int64_t>(6 * n, std::max<int64_t>(3 * nv, 3 * nt));
     const unsigned grid = (unsigned)std::min<int64_t>(std::max<int64_t>((work + 255) / 256, 1), 4096);
-    hipLaunchKernelGGL(k_seg_validate, dim3(grid), dim3(256), 0, s, seg, n, xyz, nv, tri, nt, flags);
+    hipLaunchKernelGGL(k_seg_validate, dim3(grid), dim3(256), 0, s, seg, n, xyz, nv, tri, nt, flags, box);
 }
 
-void launch_seg_mesh(const double *xyz, int64_t nv, const int32_t *tri, int64_t nt, double *P,
-                     double *tbox, double *mbox, hipStream_t s) {
-    const int64_t ntiles = (nt + MESH_TK - 1) / MESH_TK;
-    if (ntiles > 0)
-        hipLaunchKernelGGL(k_seg_mesh, dim3((unsigned)ntiles), dim3(64), 0, s, xyz, nv, tri, nt, P, tbox);
-    hipLaunchKernelGGL(k_seg_meshbox, dim3(1), dim3(64), 0, s, tbox, ntiles, mbox);
+void launch_seg_mesh(const double *xyz, int64_t nv, const int32_t *tri, int64_t nt, const SegTree &T,
+                     const unsigned long long *box, double *P, float *nodes, hipStream_t s) {
+    if (nt <= 0) return;
+    hipLaunchKernelGGL(k_seg_mesh, dim3((unsigned)((nt + 63) / 64)), dim3(64), 0, s, xyz, nv, tri, nt, box, P,
+                       (float4 *)nodes, T);
+    if (T.top >= 3) hipLaunchKernelGGL(k_seg_up, dim3(1), dim3(1024), 0, s, (float4 *)nodes, T);
 }
 
-int seg_blocks_per_cu(int mode) {
+static size_t seg_lds(const SegTree &T) { return sizeof(uint32_t) * STACK * (size_t)T.top; }
+
+int seg_blocks_per_cu(int mode, const SegTree &T) {
     int b = 0;
-    hipError_t e = mode == 0   ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_segs<0>, 64, 0)
-                   : mode == 1 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_segs<1>, 64, 0)
-                               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_segs<2>, 64, 0);
+    const size_t lds = seg_lds(T);
+    hipError_t e = mode == 0   ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_segs<0>, 64, lds)
+                   : mode == 1 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_segs<1>, 64, lds)
+                               : hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k_segs<2>, 64, lds);
     return e == hipSuccess && b > 0 ? b : 1;
 }
 
-void launch_segs(int mode, const double *seg, int64_t n, const double *P, int64_t nt, const double *tbox,
-                 const double *mbox, double r, double *dist, uint8_t *hit, const uint32_t *flags,
-                 unsigned long long *cnt, int grid, hipStream_t s) {
+void launch_segs(int mode, const double *seg, int64_t n, const double *P, int64_t nt, const SegTree &T,
+                 const float *nodes, const unsigned long long *box, double r, double *dist, uint8_t *hit,
+                 const uint32_t *flags, unsigned long long *cnt, int grid, hipStream_t s) {
     if (n <= 0) return;
     const unsigned g = (unsigned)std::min<int64_t>(grid, (n + 63) / 64);
+    const size_t lds = seg_lds(T);
+    const float4 *nd = (const float4 *)nodes;
     if (mode == 0)
-        hipLaunchKernelGGL(k_segs<0>, dim3(g), dim3(64), 0, s, seg, n, P, nt, tbox, mbox, r, dist, hit,
-                           flags, cnt);
+        hipLaunchKernelGGL(k_segs<0>, dim3(g), dim3(64), lds, s, seg, n, P, nt, nd, T, box, r, dist, hit, flags, cnt);
     else if (mode == 1)
-        hipLaunchKernelGGL(k_segs<1>, dim3(g), dim3(64), 0, s, seg, n, P, nt, tbox, mbox, r, dist, hit,
-                           flags, cnt);
+        hipLaunchKernelGGL(k_segs<1>, dim3(g), dim3(64), lds, s, seg, n, P, nt, nd, T, box, r, dist, hit, flags, cnt);
     else
-        hipLaunchKernelGGL(k_segs<2>, dim3(g), dim3(64), 0, s, seg, n, P, nt, tbox, mbox, r, dist, hit,
-                           flags, cnt);
+        hipLaunchKernelGGL(k_segs<2>, dim3(g), dim3(64), lds, s, seg, n, P, nt, nd, T, box, r, dist, hit, flags, cnt);
 }
 
 }  // namespace sd3
