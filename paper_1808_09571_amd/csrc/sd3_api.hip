@@ -160,7 +160,7 @@ struct sd3_ctx {
     std::string err;
     Workspace ws;
     Workspace sws;        // allocation-free calls: carved from the device's `scratch`
-    DevBuf mlp;           // ranker training scratch
+    DevBuf mlp;           // ranker training scratch (gradient partials)
     void *pin = nullptr;  // pinned host staging: offsets up, counters down
     size_t pin_cap = 0;
     int pairs_grid[2][2][3] = {};         // [precision][mode][tile size 32/64/128]
@@ -959,21 +959,6 @@ struct sd3_graph {
 
 namespace {
 
-MlpScratch mlp_scratch(sd3_ctx *ctx, int64_t n) {
-    int64_t m = n > 0 ? n : 1;
-    float *b = (float *)ensure(ctx->mlp, sizeof(float) * (6 * MLP_H + 2) * m);
-    MlpScratch s;
-    s.h1 = b;
-    s.h2 = b + MLP_H * m;
-    s.h3 = b + 2 * MLP_H * m;
-    s.d1 = b + 3 * MLP_H * m;
-    s.d2 = b + 4 * MLP_H * m;
-    s.d3 = b + 5 * MLP_H * m;
-    s.y = b + 6 * MLP_H * m;
-    s.dy = s.y + m;
-    return s;
-}
-
 template <typename F>
 sd3_status guarded(sd3_ctx *ctx, F f) {
     try {
@@ -1480,8 +1465,7 @@ sd3_status sd3_mlp_forward(sd3_ctx *ctx, const float *params, const float *x, in
     if (!ctx) return SD3_E_INVALID_ARG;
     if (!params || n < 0 || (n > 0 && (!x || !y))) return fail(ctx, SD3_E_INVALID_ARG, "bad MLP arguments");
     return guarded(ctx, [&] {
-        MlpScratch s = mlp_scratch(ctx, n);
-        mlp_forward(params, x, n, s, y, (hipStream_t)stream);
+        mlp_forward(params, x, n, y, (hipStream_t)stream);
     });
 }
 
@@ -1502,8 +1486,8 @@ sd3_status sd3_mlp_loss_grad(sd3_ctx *ctx, const float *params, const float *x, 
     if (!params || !loss || !grad || n < 0 || (n > 0 && (!x || !t)))
         return fail(ctx, SD3_E_INVALID_ARG, "bad MLP arguments");
     return guarded(ctx, [&] {
-        MlpScratch s = mlp_scratch(ctx, n);
-        mlp_loss_grad(params, x, t, n, s, loss, grad, (hipStream_t)stream);
+        float *part = (float *)ensure(ctx->mlp, sizeof(float) * (MLP_NPARAM + 1) * (size_t)mlp_blocks(n));
+        mlp_loss_grad(params, x, t, n, part, loss, grad, (hipStream_t)stream);
     });
 }
 

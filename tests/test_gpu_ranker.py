@@ -145,3 +145,27 @@ def test_trained_ranker_gain_on_heldout(ctx):
         assert np.array_equal(ev[o]["dist"].view(np.int64), ev["none"]["dist"].view(np.int64))
     print({o: ev[o]["tile_pairs_evaluated"] for o in ev})
     assert ev["learned"]["tile_pairs_evaluated"] <= ev["bound"]["tile_pairs_evaluated"]
+
+
+@pytest.mark.parametrize("n", [0, 15, 16, 17, 8192, 8193, 20001])
+def test_batch_edges_match_fp64_reference(ctx, n):
+    # sample counts at the edges of a block's batch of 16 and of the 512
+    # blocks after which blocks walk over several batches; repeated calls give
+    # the same bits (the partials are added in a fixed order)
+    p, X, t = _data(n + 1, max(n, 1))
+    X, t = X[:n], t[:n]
+    r = sd3.Ranker(ctx)
+    y = r.forward(_dev(p), _dev(X)).cpu().numpy()
+    loss, g = r.loss_grad(_dev(p), _dev(X), _dev(t))
+    loss2, g2 = r.loss_grad(_dev(p), _dev(X), _dev(t))
+    g, loss = g.cpu().numpy(), float(loss.item())
+    assert np.array_equal(g, g2.cpu().numpy()) and loss == float(loss2.item())
+    if n == 0:
+        assert not g.any() and loss == 0.0
+        return
+    y_ref, _ = mlp.forward(p.astype(np.float64), X.astype(np.float64))
+    l_ref, g_ref = mlp.loss_grad(p.astype(np.float64), X.astype(np.float64), t.astype(np.float64))
+    assert np.all(np.abs(y - y_ref) <= 1e-4 * (1.0 + np.abs(y_ref)))
+    assert abs(loss - l_ref) <= 1e-4 * max(1.0, l_ref)
+    assert np.linalg.norm(g - g_ref) <= 1e-4 * max(1e-6, np.linalg.norm(g_ref))
+    assert np.all(np.abs(g - g_ref) <= 1e-4 * np.abs(g_ref).max() + 1e-6)
