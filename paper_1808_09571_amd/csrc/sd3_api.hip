@@ -1201,38 +1201,23 @@ sd3_status sd3_volume(sd3_ctx *ctx, const sd3_geoms *g, double *vol, sd3_stats *
         if (st != SD3_OK) return fail(ctx, st, msg);
     }
     const int64_t G = g->count, nv = g->v_off[G], nt = g->t_off[G];
-    const int64_t CH = volume_chunk();
     hipStream_t s = (hipStream_t)stream;
     Workspace &ws = ctx->ws;
     try {
         check(hipSetDevice(ctx->device), "hipSetDevice");
-        // work items: (row, chunk) with the rows' offsets, staged in one copy:
-        // [v_off | t_off | item offsets (G+1) | first triangle of each item |
-        //  row of each item (int32)]
-        int64_t nitems = 0;
-        for (int64_t r = 0; r < G; r++) nitems += (g->t_off[r + 1] - g->t_off[r] + CH - 1) / CH;
-        const size_t bytes = sizeof(int64_t) * (3 * (G + 1) + nitems) + sizeof(int32_t) * (nitems + 1);
-        char *hs = ensure_pinned(ctx, bytes);
-        int64_t *h_voff = (int64_t *)hs, *h_toff = h_voff + (G + 1), *h_witem = h_toff + (G + 1);
-        int64_t *h_wfirst = h_witem + (G + 1);
-        int32_t *h_wrow = (int32_t *)(h_wfirst + nitems);
+        // the rows' offsets and first work items, staged in one copy:
+        // [v_off | t_off | item offsets] (G+1 each)
+        const size_t bytes = sizeof(int64_t) * 3 * (G + 1);
+        int64_t *h_voff = (int64_t *)ensure_pinned(ctx, bytes), *h_toff = h_voff + (G + 1), *h_witem = h_toff + (G + 1);
         memcpy(h_voff, g->v_off, sizeof(int64_t) * (G + 1));
         memcpy(h_toff, g->t_off, sizeof(int64_t) * (G + 1));
-        int64_t it = 0;
-        for (int64_t r = 0; r < G; r++) {
-            h_witem[r] = it;
-            for (int64_t t = g->t_off[r]; t < g->t_off[r + 1]; t += CH) {
-                h_wfirst[it] = t;
-                h_wrow[it] = (int32_t)r;
-                it++;
-            }
-        }
-        h_witem[G] = it;
-        char *ds = (char *)ensure(ws.vol_items, bytes + 64);
-        check(hipMemcpyAsync(ds, hs, bytes, hipMemcpyHostToDevice, s), "H2D volume items");
-        const int64_t *d_voff = (const int64_t *)ds, *d_toff = d_voff + (G + 1), *d_witem = d_toff + (G + 1);
-        const int64_t *d_wfirst = d_witem + (G + 1);
-        const int32_t *d_wrow = (const int32_t *)(d_wfirst + nitems);
+        h_witem[0] = 0;
+        for (int64_t r = 0; r < G; r++)
+            h_witem[r + 1] = h_witem[r] + volume_items(g->t_off[r + 1] - g->t_off[r], g->v_off[r + 1] - g->v_off[r]);
+        const int64_t nitems = h_witem[G];
+        int64_t *d_voff = (int64_t *)ensure(ws.vol_items, bytes + 64);
+        check(hipMemcpyAsync(d_voff, h_voff, bytes, hipMemcpyHostToDevice, s), "H2D volume items");
+        const int64_t *d_toff = d_voff + (G + 1), *d_witem = d_toff + (G + 1);
         const double *xyz = g->xyz;
         const int32_t *tri = g->tri;
         if (g->mem == SD3_MEM_HOST) {
@@ -1250,8 +1235,7 @@ sd3_status sd3_volume(sd3_ctx *ctx, const sd3_geoms *g, double *vol, sd3_stats *
         double *dvol = g->mem == SD3_MEM_HOST ? (double *)((char *)part + 16 * (size_t)(nitems > 0 ? nitems : 1))
                                               : vol;
         unsigned int *sc = (unsigned int *)ensure(ws.scalars, SCALAR_BYTES);
-        launch_volume(xyz, nv, tri, d_voff, d_toff, d_wrow, d_wfirst, nitems, d_witem, G, part, dvol,
-                      (uint32_t *)sc, ctx->cus * 8, s);
+        launch_volume(xyz, tri, d_voff, d_toff, nitems, d_witem, G, part, dvol, (uint32_t *)sc, s);
         check(hipGetLastError(), "kernel launch");
         char *rb = readback_area(ctx);
         check(hipMemcpyAsync(rb, sc, 4, hipMemcpyDeviceToHost, s), "D2H flags");

@@ -95,3 +95,19 @@ def test_volume_errors(ctx):
         with pytest.raises(sd3.SD3Error) as e:
             _vol(ctx, [broken, m], dev)
         assert e.value.name == "SD3_E_INDEX_RANGE"
+
+
+def test_chunk_edges(ctx):
+    # rows at the edges of a work item's 4096 triangles and of a block's
+    # batches of 1024, beside empty ones; a bad coordinate in a row of vertices
+    # alone is still refused
+    meshes = [synth.random_triangle_soup(n, 7 + n, scale=1.0) if n else (np.zeros((0, 3)), np.zeros((0, 3), np.int32))
+              for n in (1, 0, 1023, 1024, 1025, 4095, 4096, 4097, 0, 8193)]
+    v = _vol(ctx, meshes, True)
+    assert np.array_equal(v.view(np.int64), _vol(ctx, meshes, False).view(np.int64))
+    _check(meshes, v)
+    lone = (np.array([[0.0, 1.0, np.nan]]), np.zeros((0, 3), np.int32))
+    for dev in (False, True):
+        with pytest.raises(sd3.SD3Error) as e:
+            _vol(ctx, [meshes[0], lone], dev)
+        assert e.value.name == "SD3_E_NONFINITE"
