@@ -2186,19 +2186,23 @@ __device__ __forceinline__ void global_push(bool keep, const T &item, T *arr, un
 
 
 constexpr int QB = 16;      // most queue entries a wave claims at once
-constexpr int RING = 128;   // LDS ring of triangle pairs awaiting their test (two batches)
-constexpr int TLCAP = 192;  // FP32 pairs awaiting the rescue decision of their tile pair
+constexpr int RING = 128;   // LDS rings of triangle pairs awaiting a batch of 64 (two batches)
+constexpr int TLCAP = 128;  // FP32 pairs awaiting the rescue decision of their tile pair
 constexpr unsigned RCHUNK = 128;  // rescue-list slots a wave claims at once
 
 // Lane i's value in every lane (i wave-uniform): v_readlane into a scalar.
-__device__ __forceinline__ int rl_i(int v, int i) { return __builtin_amdgcn_readlane(v, i); }
-__device__ __forceinline__ float rl_f(float v, int i) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
-}
 __device__ __forceinline__ unsigned long long rl_u64(unsigned long long b, int i) {
     const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, i);
     const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), i);
     return ((unsigned long long)hi << 32) | lo;
+}
+// A value every lane holds (a broadcast LDS read), as a scalar.
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ float uni(float v) { return __int_as_float(uni(__float_as_int(v))); }
+__device__ __forceinline__ double uni(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)uni((int)b), hi = (unsigned)uni((int)(b >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 __device__ __forceinline__ double rl_d(double v, int i) {
     return __longlong_as_double((long long)rl_u64((unsigned long long)__double_as_longlong(v), i));
@@ -2239,19 +2243,20 @@ struct RescueChunk {
     }
 };
 
-// One claimed queue entry, held in the registers of the lane of its index in
-// the wave's batch: its tiles, row and counts, the row's state when the batch
+// One claimed queue entry of the wave's batch (gathered by the lane of its
+// index, kept in LDS): its tiles, row and counts, the row's state when the batch
 // was gathered (a stale upper bound is still an upper bound: it only prunes
 // less), and the FP32 constants of the tile pair.
 struct Entry {
     int ta, tb, g, na, nb, seed_q, hit;
     float lbf;
     double ub, msc;  // row upper bound and margin scale
+    float ax0, ax1, ax2;  // distance: unit vector from the A tile's box centre to the B tile's (0: none)
     float sh0, sh1, sh2, eu, elb, eps_f, box_tol;
     double eps_c;
 };
 
-// Gathers entry q0 + lane of the batch into lane `lane`'s registers (lanes at
+// Gathers entry q0 + lane of the batch in lane `lane` (lanes at
 // and beyond the batch size keep ta = -1).  In the seed pass entry g is row
 // g's chosen queue entry.  Returns 1 in the lanes whose two tiles name
 // different rows (an inconsistency the caller counts; never expected).
@@ -2290,6 +2295,17 @@ __device__ __forceinline__ int wave_gather(Entry &E, const Lists &L, unsigned qc
             E.seed_q = R.seed_q;
             E.ub = bits_to_double(R.ub);
             E.msc = R.margin_scale;
+            if (MODE == 0) {
+                double d[3], l = 0.0;
+                for (int k = 0; k < 3; k++) {
+                    d[k] = (b.lo[k] + b.hi[k]) - (a.lo[k] + a.hi[k]);
+                    l += d[k] * d[k];
+                }
+                l = l > 0.0 && l < __builtin_inf() ? 1.0 / sqrt(l) : 0.0;
+                E.ax0 = (float)(d[0] * l);
+                E.ax1 = (float)(d[1] * l);
+                E.ax2 = (float)(d[2] * l);
+            }
             if (PREC == 0) {
                 // B is shifted into A's frame, so that A's staged copy serves
                 // every consecutive entry of the same A tile
@@ -2315,44 +2331,74 @@ __device__ __forceinline__ double fp32_upper(float dm, float eu) {
     return U * (1.0 + 4.0 * U64);
 }
 
-// One wave per tile pair.  Each wave claims batches of up to QB queue
-// entries (its first batch is its static share, later ones come from the
-// shared head, claimed one batch ahead so the atomic's latency overlaps the
-// current batch), gathers them into its lanes' registers, and evaluates them
-// one by one.  The global loads of the next live entry's two tiles (and of
-// its row's current upper bound) are issued as soon as the current entry is
-// staged, so they travel while the current entry is culled and tested.  Per
-// entry: both tiles staged into the wave's own LDS (FP32 copies, the B tile
-// shifted into the A tile's frame, or FP64; the A tile is kept when the
-// previous entry staged the same one), a cull of 8 x 8 slot-group boxes, then of
-// triangle boxes, with the surviving triangle pairs compacted by ballots into
-// an LDS ring and tested 64 at a time, one pair per lane.  Distance: the wave
-// lowers the row bound with one atomic whose result it does not wait for,
-// and rescues the FP32 pairs whose certified lower bound does not exceed the
-// smaller of the row bound read at staging and its own upper bound (plus
-// margin); intersects: certified hits set the row flag, undecided pairs go
-// to the rescue (FP32) or exact (FP64) list.  Nothing is shared between
-// waves but the queue head, the rows' state and the lists, so there is no
-// workgroup barrier.
+// Whether two point sets are certainly farther apart than lim by their
+// separation sep = min u . b - max u . a along u (uu = |u|^2): FP32 copies,
+// with elb bounding the copies' distance from the real points plus the
+// rounding (at most sqrt(3) * 8 roundings of the largest offset here, elb
+// holds 16).  A direction too short for its square to keep full precision
+// decides nothing, nor does a NaN.
+__device__ __forceinline__ bool axis_far32(float sep, float uu, float elb, float limf) {
+    return uu >= 0x1p-120f && sep * __builtin_amdgcn_rsqf(uu) - elb > limf;
+}
+// FP64: the rounding (2^-47 of the extent) is far below the margin in T2
+// (2^-36 of it).
+__device__ __forceinline__ bool axis_far64(double sep, double uu, double T2) {
+    return sep > 0.0 && sep * sep > T2 * uu * (1.0 + 16.0 * U64);
+}
+
+// One wave per tile pair.  Each wave takes batches of up to QB queue entries
+// (its first batch is its static share; later ones are dealt out in turn or
+// come from the shared head, claimed one batch ahead so the atomic's latency
+// overlaps the current batch), gathers them into LDS, and evaluates them one by
+// one.  Per entry: the raw corners of both tiles are loaded (FP32 copies, or
+// FP64), with the row's state now.  Distance: the tiles' separation along the
+// line of their box centres comes first and ends two thirds of the tile pairs
+// whose boxes were near enough.  The others are staged into the wave's own LDS
+// (the B tile shifted into the A tile's frame; a staged A tile is kept for the
+// next entry of the same one), a cull of 8 x 8 slot-group boxes follows, then
+// of triangle boxes, then (distance) of the pairs' separation along the line
+// of their centres, each stage's survivors compacted by ballots into an LDS
+// ring and taken 64 at a time, one pair per lane; the few that are left get
+// the full test.  Distance: each batch's minimum tightens the thresholds of
+// what remains of the tile pair, the wave lowers the row bound with one atomic
+// whose result it does not wait for, and rescues the FP32 pairs whose
+// certified lower bound does not exceed the smaller of the row bound read with
+// the tiles and its own upper bound (plus margin); intersects: certified hits
+// set the row flag and end the row, undecided pairs go to the rescue (FP32) or
+// exact (FP64) list.  Nothing is shared between waves but the queue head, the
+// rows' state and the lists, so there is no workgroup barrier.
+//
+// Bound by vector instructions and, for queues of a few entries a wave, by the
+// latency of one tile pair (about 12 us).  The axis tests are what the full
+// test costs least without: of the 31 triangle pairs whose boxes are near
+// enough in a tile pair of the tube/blob column, one is left.  Full tests of
+// the 4096-row column 6.4e7 -> 9.5e6 per call, this kernel 3.5 -> 1.5 ms (64
+// triangles a tile, FP32); plain FP64 over 250 rows 1.32 -> 0.48 ms; LDS 20.4
+// -> 12.4 KB a wave (FP32), 38.4 -> 19.5 KB (FP64), which with the registers
+// allows three and two waves a SIMD instead of two and one.
 template <int PREC, int MODE, int TK>
-__global__ __launch_bounds__(64) void k_pairs(const float *t32A, const double *t64A,
+__global__ __launch_bounds__(64, PREC == 0 && TK <= 64 ? 3 : 1) void k_pairs(const float *t32A, const double *t64A,
                                               const TileMeta *mA, const float *t32B,
                                               const double *t64B, const TileMeta *mB,
                                               RowState *rows, Lists L) {
     static_assert(tile_size_ok(TK), "tile size");
-    constexpr int NF = F_NTRI32;
+    constexpr int VS = PREC == 0 ? 12 : 10;  // a staged slot's corners (9), 16-byte aligned
     constexpr int NG = TK / 8, NGP = NG * NG;
     constexpr int NS = 2 * TK / 64;  // staging slots per lane: [A slots | B slots]
     constexpr bool TESTED_LIST = PREC == 0 && MODE == 0;
     using Tt = typename std::conditional<PREC == 0, float, double>::type;
-    // the staged tiles, slot-major: a slot's NF fields are contiguous, so a
-    // triangle's fields are read with 16-byte LDS loads
-    __shared__ __attribute__((aligned(16))) Tt sA[NF * TK];
-    __shared__ __attribute__((aligned(16))) Tt sB[NF * TK];
+    // the staged tiles, slot-major (a slot's values contiguous: 16-byte LDS
+    // loads), corners and boxes; what a full test derives from the corners it
+    // forms itself, in registers: about ten pairs of a tile pair reach one, and
+    // the 21 derived fields of every slot held the kernel to two waves a SIMD
+    __shared__ __attribute__((aligned(16))) Tt sA[VS * TK], sB[VS * TK];
+    __shared__ __attribute__((aligned(16))) Tt xA[6 * TK], xB[6 * TK];  // lo xyz, hi xyz
     __shared__ Tt gbox[2][NG][6];  // [side][group][lo xyz, hi xyz]
     __shared__ uint32_t glist[NGP];
-    __shared__ uint32_t ring[RING];
+    __shared__ uint16_t ring[RING];  // (a slot | b slot << 8): pairs whose boxes are near enough
+    __shared__ uint16_t rdy[MODE == 0 ? RING : 1];  // distance: those no axis separates, to be tested
     __shared__ uint32_t tl[TESTED_LIST ? TLCAP : 1];
+    __shared__ Entry ents[QB];  // the claimed batch
     const int lane = lane_id();
     const unsigned long long below = lanes_below();
     const unsigned qcount = L.seed_pass ? (unsigned)L.nrows : min(*L.qcount, L.qcap);
@@ -2360,80 +2406,150 @@ __global__ __launch_bounds__(64) void k_pairs(const float *t32A, const double *t
     // entries per claim: 1 for short queues (every wave starts at once), up
     // to QB for long ones (one atomic and one gather per batch)
     const unsigned qb = max(1u, min((unsigned)QB, qcount / (nwave * 4u)));
+    // a short queue is dealt out in turn: the claims, all on one address, cost
+    // about 8 ns each and set the time of a call whose waves take a few entries
+    // (solid columns of 9,000 entries 357 -> 262 us, a 25,000-entry intersects
+    // pass 215 -> 112 us); a long one is claimed, since its tile pairs' costs
+    // differ (1.1M entries: 1.52 ms claimed, 1.65 ms dealt out)
+    const bool strided = qcount <= (unsigned)QB * nwave;
     unsigned long long n_eval = 0, n_boxed = 0, n_tested = 0, n_resc = 0, n_exact = 0, n_bad = 0;
     RescueChunk rch;
     int staged_a = -1;  // the A tile whose copy is in sA (wave-uniform)
+    int hit_row = -1;   // the last row this wave found to meet (wave-uniform)
     unsigned claim = blockIdx.x;
     for (;;) {
         const unsigned q0 = claim * qb;
         if (q0 >= qcount) break;
-        Entry E;
-        n_bad += wave_gather<PREC, MODE>(E, L, qcount, mA, mB, rows, q0, qb);
-        unsigned nxt = 0;
-        if (lane == 0) nxt = nwave + atomicAdd(L.qhead, 1u);
-        const int bn = (int)min(qb, qcount - q0);
+        wave_lds_sync();  // the previous batch's reads
         // entry i is evaluated unless its row has no seed choice, already
         // meets, was seeded with it, or its box bound exceeds the row bound
-        // (plus margin) gathered with the batch (wave-uniform)
-        auto live = [&](int i) __attribute__((always_inline)) {
-            if (rl_i(E.ta, i) < 0 || rl_i(E.hit, i)) return false;
-            if (!L.seed_pass && (int)(q0 + (unsigned)i) == rl_i(E.seed_q, i)) return false;
-            if (MODE == 0) {
-                const double ub = rl_d(E.ub, i), msc = rl_d(E.msc, i);
-                if ((double)rl_f(E.lbf, i) > ub + msc + 1.4551915228366852e-11 * ub) return false;
-            }
-            return true;
+        // (plus margin) gathered with the batch
+        unsigned long long live;
+        {
+            Entry E;
+            n_bad += wave_gather<PREC, MODE>(E, L, qcount, mA, mB, rows, q0, qb);
+            bool on = E.ta >= 0 && !E.hit && (L.seed_pass || (int)(q0 + (unsigned)lane) != E.seed_q);
+            if (MODE == 0) on = on && !((double)E.lbf > E.ub + E.msc + 1.4551915228366852e-11 * E.ub);
+            live = __ballot(on);
+            if (lane < QB) ents[lane] = E;
+        }
+        wave_lds_sync();
+        unsigned nxt = 0;
+        if (strided) nxt = claim + nwave;
+        else if (lane == 0) nxt = nwave + atomicAdd(L.qhead, 1u);
+        const int bn = (int)min(qb, qcount - q0);
+        // the next live entry at or after i
+        auto next_live = [&](int i) __attribute__((always_inline)) {
+            const unsigned long long m = i < 64 ? live >> i : 0ull;
+            return m ? i + (int)__ffsll(m) - 1 : bn;
         };
-        // raw tile data of the entry staged next (its A tile only when that
-        // is not the one staged already), and its row's upper bound
-        Tt raw[NS][9];
-        unsigned long long raw_ub = ~0ull;
-        int pf = -1;
-        bool raw_keepA = false;
-        auto load_raw = [&](int j) __attribute__((always_inline)) {
-            const int ja = rl_i(E.ta, j), jb = rl_i(E.tb, j);
-            raw_keepA = ja == staged_a;
+        // a tile pair's raw corners (its A tile only when it is not the one at
+        // hand already) and its row's state now
+        auto load_raw = [&](int ja, int jb, int g, Tt(&dst)[NS][9], unsigned long long &dub, uint32_t &dhit,
+                            bool skip_a) __attribute__((always_inline)) {
 #pragma unroll
             for (int s = 0; s < NS; s++) {
                 const int sl = s * 64 + lane;
                 const bool onB = sl >= TK;
-                if (!onB && raw_keepA) continue;
+                if (!onB && skip_a) continue;
                 const int jj = onB ? sl - TK : sl;
                 const Tt *src = PREC == 0 ? (const Tt *)(onB ? t32B + (int64_t)jb * 9 * TK : t32A + (int64_t)ja * 9 * TK)
                                           : (const Tt *)(onB ? t64B + (int64_t)jb * 9 * TK : t64A + (int64_t)ja * 9 * TK);
 #pragma unroll
-                for (int c = 0; c < 9; c++) raw[s][c] = src[c * TK + jj];
+                for (int c = 0; c < 9; c++) dst[s][c] = src[c * TK + jj];
             }
-            if (MODE == 0) raw_ub = rows[rl_i(E.g, j)].ub;
-            pf = j;
+            const RowState *R = rows + g;
+            if (MODE == 0) dub = R->ub;
+            dhit = R->hit;
         };
-        int i = 0;
-        while (i < bn && !live(i)) i++;
-        for (; i < bn;) {
-            if (pf != i) load_raw(i);
-            const int ta = rl_i(E.ta, i), tb = rl_i(E.tb, i), g = rl_i(E.g, i);
-            const int na = rl_i(E.na, i), nb = rl_i(E.nb, i);
-            const float lbf = rl_f(E.lbf, i);
-            const double msc = rl_d(E.msc, i);
+        for (int i = next_live(0); i < bn; i = next_live(i + 1)) {
+            const Entry e = ents[i];
+            const int ta = uni(e.ta), tb = uni(e.tb), g = uni(e.g);
+            if (g == hit_row) continue;
+            Tt raw[NS][9];
+            unsigned long long raw_ub = 0;
+            uint32_t raw_hit = 0;
+            const bool keepA = staged_a == ta;
+            load_raw(ta, tb, g, raw, raw_ub, raw_hit, MODE == 1 && keepA);
+            if (uni((int)raw_hit)) continue;
             n_eval++;
+            const int na = uni(e.na), nb = uni(e.nb);
+            const float lbf = uni(e.lbf);
+            const double msc = uni(e.msc);
             float sh[3] = {0.0f, 0.0f, 0.0f}, eu = 0.0f, elb = 0.0f, eps_f = 0.0f, box_tol = 0.0f;
             double eps_c = 0.0;
             if (PREC == 0) {
-                sh[0] = rl_f(E.sh0, i);
-                sh[1] = rl_f(E.sh1, i);
-                sh[2] = rl_f(E.sh2, i);
-                eu = rl_f(E.eu, i);
-                elb = rl_f(E.elb, i);
-                eps_f = rl_f(E.eps_f, i);
-                box_tol = rl_f(E.box_tol, i);
-                eps_c = rl_d(E.eps_c, i);
+                sh[0] = uni(e.sh0);
+                sh[1] = uni(e.sh1);
+                sh[2] = uni(e.sh2);
+                eu = uni(e.eu);
+                elb = uni(e.elb);
+                eps_f = uni(e.eps_f);
+                box_tol = uni(e.box_tol);
+                eps_c = uni(e.eps_c);
+            }
+            // the row bound now: the batch's, or the one read with the tiles
+            double ub = uni(e.ub);
+            if (MODE == 0) ub = fmin(ub, bits_to_double(rl_u64(raw_ub, 0)));
+            // cull thresholds of the row bound (see sd3_pair32.h for eps_c)
+            float T2f = 0.0f, limf = 0.0f;
+            double T2d = 0.0;
+            auto set_limits = [&]() __attribute__((always_inline)) {
+                const double m = msc + 1.4551915228366852e-11 * ub;
+                if (PREC == 0) {
+                    const double T = (ub + m + eps_c) / (1.0 - 4.0 * U32);
+                    const double T2 = T * T * (1.0 + 16.0 * U32);
+                    T2f = T2 < 3.0e38 ? (float)(T2 * (1.0 + 0x1p-20)) : __builtin_inff();
+                    limf = (float)((ub + m) * (1.0 + 0x1p-20));
+                } else {
+                    const double T = (ub + m) * (1.0 + 8.0 * U64);
+                    T2d = T * T;
+                }
+            };
+            if (MODE == 0) set_limits();
+            // distance: the two tiles' separation along the line of their box
+            // centres, from the raw corners.  Two thirds of the tile pairs
+            // whose boxes are near enough end here, before anything is staged
+            // (tiles lie across the axes)
+            if (MODE == 0) {
+                const Tt u[3] = {(Tt)uni(e.ax0), (Tt)uni(e.ax1), (Tt)uni(e.ax2)};
+                // FP32 copies are offsets in A's frame (B shifted into it);
+                // FP64 corners are taken from the A tile's first
+                Tt off[3];
+#pragma unroll
+                for (int k = 0; k < 3; k++) {
+                    if constexpr (PREC == 0) off[k] = sh[k];
+                    else off[k] = -rl_d(raw[0][k], 0);
+                }
+                Tt amax = -(Tt)__builtin_inf(), bmin = (Tt)__builtin_inf();
+#pragma unroll
+                for (int s = 0; s < NS; s++) {
+                    const bool onB = s * 64 + lane >= TK;
+#pragma unroll
+                    for (int k = 0; k < 3; k++) {
+                        Tt x = 0;
+#pragma unroll
+                        for (int c = 0; c < 3; c++)
+                            x += u[c] * (raw[s][3 * k + c] + (PREC == 1 || onB ? off[c] : (Tt)0));
+                        amax = onB ? amax : fmax(amax, x);
+                        bmin = onB ? fmin(bmin, x) : bmin;
+                    }
+                }
+                const Tt sep = wave_min(bmin) - wave_max(amax), uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+                const bool far = PREC == 0 ? axis_far32((float)sep, (float)uu, elb, limf)
+                                           : axis_far64((double)sep, (double)uu, T2d);
+                if (far) {
+                    // (every pair lies beyond the threshold)
+                    if (L.log && lane == 0)
+                        log_tile_pair(L, mA[ta], mB[tb], rows[g].scale, lbf, sqrt(PREC == 0 ? (double)T2f : T2d), g);
+                    continue;
+                }
             }
             // stage both tiles from the raw registers: slot s of [A slots |
             // B slots], 64 at a time; each group of 8 consecutive slots (8
             // lanes) reduces its box.  An A tile that is already staged (the
             // previous entry's) is kept: A stays in its own frame and B is
             // shifted into it
-            const bool keepA = raw_keepA;
             staged_a = ta;
 #pragma unroll
             for (int s = 0; s < NS; s++) {
@@ -2442,8 +2558,6 @@ __global__ __launch_bounds__(64) void k_pairs(const float *t32A, const double *t
                 if (!onB && keepA) continue;
                 const int j = onB ? sl - TK : sl;
                 Tt *dst = onB ? sB : sA;
-                // the vertices in registers: stored, and every derived field
-                // and the triangle box computed from them (no LDS read back)
                 Tt v[9];
                 if (PREC == 0) {
                     const float sx = onB ? sh[0] : 0.0f, sy = onB ? sh[1] : 0.0f, sz = onB ? sh[2] : 0.0f;
@@ -2454,23 +2568,16 @@ __global__ __launch_bounds__(64) void k_pairs(const float *t32A, const double *t
                     for (int c = 0; c < 9; c++) v[c] = raw[s][c];
                 }
 #pragma unroll
-                for (int c = 0; c < 9; c++) dst[j * NF + c] = v[c];
+                for (int c = 0; c < 9; c++) dst[j * VS + c] = v[c];
                 Tt bx[6];
 #pragma unroll
                 for (int k = 0; k < 3; k++) {
                     bx[k] = fmin(v[k], fmin(v[3 + k], v[6 + k]));
                     bx[3 + k] = fmax(v[k], fmax(v[3 + k], v[6 + k]));
                 }
-                if constexpr (PREC == 0) {
-                    tri_derive32(TriRef<float>{(float *)dst + j * NF, 1}, v);
-                } else {
-                    tri_derive64(TriRef<double>{(double *)dst + j * NF, 1}, v);
+                Tt *xd = (onB ? xB : xA) + j * 6;
 #pragma unroll
-                    for (int k = 0; k < 3; k++) {
-                        dst[j * NF + F_LO + k] = bx[k];
-                        dst[j * NF + F_HI + k] = bx[3 + k];
-                    }
-                }
+                for (int k = 0; k < 6; k++) xd[k] = bx[k];
                 if constexpr (PREC == 0) {
 #pragma unroll
                     for (int k = 0; k < 3; k++) {
@@ -2489,27 +2596,6 @@ __global__ __launch_bounds__(64) void k_pairs(const float *t32A, const double *t
                 if ((j & 7) == 0)
 #pragma unroll
                     for (int k = 0; k < 6; k++) gbox[onB ? 1 : 0][j >> 3][k] = bx[k];
-            }
-            // the row bound now: the batch's, or the one read with the tiles
-            double ub = rl_d(E.ub, i);
-            if (MODE == 0) ub = fmin(ub, bits_to_double(rl_u64(raw_ub, 0)));
-            // the next live entry's loads travel while this one is worked
-            // (FP32 tiles; the FP64 copies would take twice the registers)
-            int nx = i + 1;
-            while (nx < bn && !live(nx)) nx++;
-            if (PREC == 0 && nx < bn) load_raw(nx);
-            float T2f = 0.0f;
-            double T2d = 0.0;
-            if (MODE == 0) {
-                const double m = msc + 1.4551915228366852e-11 * ub;
-                if (PREC == 0) {
-                    const double T = (ub + m + eps_c) / (1.0 - 4.0 * U32);
-                    const double T2 = T * T * (1.0 + 16.0 * U32);
-                    T2f = T2 < 3.0e38 ? (float)(T2 * (1.0 + 0x1p-20)) : __builtin_inff();
-                } else {
-                    const double T = (ub + m) * (1.0 + 8.0 * U64);
-                    T2d = T * T;
-                }
             }
             wave_lds_sync();
             // group-box pairs, compacted into glist
@@ -2540,7 +2626,7 @@ __global__ __launch_bounds__(64) void k_pairs(const float *t32A, const double *t
             // their triangle-box test into the ring; full batches of 64 are
             // tested at once
             Tt tmin = (Tt)__builtin_inf();
-            unsigned rc = 0, rd = 0, tc = 0;
+            unsigned rc = 0, rd = 0, rt = 0, re = 0, tc = 0;
             auto rescue_tested = [&](double lim) __attribute__((always_inline)) {
                 // every lane runs every round (the chunk state stays uniform)
                 for (unsigned k0 = 0; k0 < tc; k0 += 64) {
@@ -2554,11 +2640,22 @@ __global__ __launch_bounds__(64) void k_pairs(const float *t32A, const double *t
             };
             auto test_batch = [&](unsigned n) __attribute__((always_inline)) {
                 const bool on = (unsigned)lane < n;
-                uint32_t e = on ? ring[(rd + lane) & (RING - 1)] : 0u;
-                const int a = e & 255, b = (e >> 8) & 255;
-                if (PREC == 0) {
-                    TriRef<float> TA{(float *)sA + a * NF, 1}, TB{(float *)sB + b * NF, 1};
+                uint32_t pr = 0;
+                if (on) pr = MODE == 0 ? rdy[(re + lane) & (RING - 1)] : ring[(rd + lane) & (RING - 1)];
+                const int a = pr & 255, b = (pr >> 8) & 255;
+                n_tested += n;
+                const Tt *pa = sA + a * VS, *pb = sB + b * VS;
+                if constexpr (PREC == 0) {
+                    float fa[F_NTRI32], fb[F_NTRI32];
+                    TriRef<float> TA{fa, 1}, TB{fb, 1};
+#pragma unroll
+                    for (int k = 0; k < 9; k++) {
+                        fa[F_V + k] = pa[k];
+                        fb[F_V + k] = pb[k];
+                    }
                     if (MODE == 0) {
+                        tri_prep32(TA);
+                        tri_prep32(TB);
                         uint32_t te = 0;
                         if (on) {
                             const Pair32 r = pair32(TA, TB, elb);
@@ -2581,20 +2678,33 @@ __global__ __launch_bounds__(64) void k_pairs(const float *t32A, const double *t
                         tc += n;
                     } else {
                         int c = 0;
-                        if (on) {
-                            c = isect32(TA, TB, eps_f);
-                            // not settled by planes and crossings: a certified
-                            // separating plane along the closest direction
-                            // still proves the pair disjoint
-                            if (c == 2 && pair32(TA, TB, elb).lb > 0.0f) c = 0;
+                        if (on) c = isect32(pa, pb, xA + a * 6, xB + b * 6, eps_f);
+                        // not settled by planes and crossings: a certified
+                        // separating plane along the closest direction still
+                        // proves the pair disjoint
+                        if (c == 2) {
+                            tri_prep32(TA);
+                            tri_prep32(TB);
+                            if (pair32(TA, TB, elb).lb > 0.0f) c = 0;
                         }
-                        if (__ballot(c == 1) && lane == 0) atomicOr(&rows[g].hit, 1u);
+                        if (__ballot(c == 1)) {
+                            if (lane == 0) atomicOr(&rows[g].hit, 1u);
+                            hit_row = g;
+                        }
                         Rescue it{ta, tb, (uint32_t)(a | (b << 16)), 0.0f};
                         rch.push(c == 2, it, L);
                         n_resc += c == 2;
                     }
                 } else {
-                    TriRef<double> TA{(double *)sA + a * NF, 1}, TB{(double *)sB + b * NF, 1};
+                    double fa[F_NTRI64], fb[F_NTRI64];
+                    TriRef<double> TA{fa, 1}, TB{fb, 1};
+#pragma unroll
+                    for (int k = 0; k < 9; k++) {
+                        fa[F_V + k] = pa[k];
+                        fb[F_V + k] = pb[k];
+                    }
+                    tri_prep64(TA);
+                    tri_prep64(TB);
                     // distance and intersects both use the full FP64 pair test:
                     // its separating-plane certificate settles the disjoint
                     // pairs whose orientation signs are exact zeros
@@ -2606,23 +2716,80 @@ __global__ __launch_bounds__(64) void k_pairs(const float *t32A, const double *t
                         d2 = r.d2;
                         if (MODE == 0) tmin = fmin(tmin, (Tt)r.d2);
                     }
-                    if (__ballot(st == 1) && lane == 0) atomicOr(&rows[g].hit, 1u);
+                    if (__ballot(st == 1)) {
+                        if (lane == 0) atomicOr(&rows[g].hit, 1u);
+                        hit_row = g;
+                    }
                     ExactItem it{ta, tb, (uint32_t)(a | (b << 16)), 0, d2};
                     global_push(st == 2, it, L.exact, L.xcount, L.xcap);
                     n_exact += st == 2;
                 }
+                if (MODE == 0) re += n;
+                else rd += n;
+            };
+            // distance: the next n box survivors through the separation of
+            // their corners along the line of their centres; a pair farther
+            // apart than the row bound (plus margin) that way is dropped, the
+            // others await the full test
+            auto sat_batch = [&](unsigned n) __attribute__((always_inline)) {
+                const bool on = (unsigned)lane < n;
+                const uint32_t pr = on ? ring[(rd + lane) & (RING - 1)] : 0u;
+                const Tt *pa = sA + (pr & 255) * VS, *pb = sB + (pr >> 8) * VS;
+                Tt u[3], uu = 0, amax = 0, bmin = 0;
+#pragma unroll
+                for (int k = 0; k < 3; k++) {
+                    u[k] = (pb[k] + pb[3 + k] + pb[6 + k]) - (pa[k] + pa[3 + k] + pa[6 + k]);
+                    uu += u[k] * u[k];
+                }
+#pragma unroll
+                for (int k = 0; k < 3; k++) {
+                    const Tt x = u[0] * pa[3 * k] + u[1] * pa[3 * k + 1] + u[2] * pa[3 * k + 2];
+                    const Tt y = u[0] * pb[3 * k] + u[1] * pb[3 * k + 1] + u[2] * pb[3 * k + 2];
+                    amax = k == 0 ? x : fmax(amax, x);
+                    bmin = k == 0 ? y : fmin(bmin, y);
+                }
+                const Tt sep = bmin - amax;
+                const bool far = PREC == 0 ? axis_far32((float)sep, (float)uu, elb, limf)
+                                           : axis_far64((double)sep, (double)uu, T2d);
+                const bool keep = on && !far;
+                const unsigned long long mk = __ballot(keep);
+                if (keep) rdy[(rt + __popcll(mk & below)) & (RING - 1)] = (uint16_t)pr;
+                rt += (unsigned)__popcll(mk);
                 rd += n;
             };
-            for (unsigned gi = 0; gi < gcnt; gi++) {
-                const uint32_t ge = glist[gi];
+            // the latest stage with a full batch first, each stage's rest when
+            // the one before it is done; a row found to meet ends it
+            for (unsigned gi = 0; g != hit_row;) {
+                if (MODE == 0 && rt > re && (rt - re >= 64 || (gi == gcnt && rc == rd))) {
+                    wave_lds_sync();
+                    test_batch(min(rt - re, 64u));
+                    if (rt > re || rc > rd || gi < gcnt) {
+                        // the pairs that remain meet the bound this batch left
+                        const Tt dm = wave_min(tmin);
+                        if (dm < (Tt)__builtin_inf()) {
+                            const double U = PREC == 0 ? fp32_upper((float)dm, eu) : sqrt((double)dm);
+                            if (U < ub) {
+                                ub = U;
+                                set_limits();
+                            }
+                        }
+                    }
+                    continue;
+                }
+                if (rc > rd && (rc - rd >= 64 || gi == gcnt)) {
+                    wave_lds_sync();
+                    if (MODE == 0) sat_batch(min(rc - rd, 64u));
+                    else test_batch(min(rc - rd, 64u));
+                    continue;
+                }
+                if (gi == gcnt) break;
+                const uint32_t ge = glist[gi++];
                 const int a = (int)(ge & 255) * 8 + (lane >> 3);
                 const int b = (int)((ge >> 8) & 255) * 8 + (lane & 7);
                 bool keep = a < na && b < nb;
-                const Tt *pa = sA + a * NF, *pb = sB + b * NF;
-                const Tt alo[3] = {pa[F_LO], pa[F_LO + 1], pa[F_LO + 2]};
-                const Tt ahi[3] = {pa[F_HI], pa[F_HI + 1], pa[F_HI + 2]};
-                const Tt blo[3] = {pb[F_LO], pb[F_LO + 1], pb[F_LO + 2]};
-                const Tt bhi[3] = {pb[F_HI], pb[F_HI + 1], pb[F_HI + 2]};
+                const Tt *pa = xA + a * 6, *pb = xB + b * 6;
+                const Tt alo[3] = {pa[0], pa[1], pa[2]}, ahi[3] = {pa[3], pa[4], pa[5]};
+                const Tt blo[3] = {pb[0], pb[1], pb[2]}, bhi[3] = {pb[3], pb[4], pb[5]};
                 if (MODE == 0) {
                     const Tt g2 = gap2_boxes(alo, ahi, blo, bhi);
                     keep = keep && (PREC == 0 ? (float)g2 <= T2f : (double)g2 <= T2d);
@@ -2630,18 +2797,13 @@ __global__ __launch_bounds__(64) void k_pairs(const float *t32A, const double *t
                     keep = keep && overlap_boxes(alo, ahi, blo, bhi, PREC == 0 ? (Tt)box_tol : (Tt)0);
                 }
                 const unsigned long long mk = __ballot(keep);
-                if (keep) ring[(rc + __popcll(mk & below)) & (RING - 1)] = (uint32_t)(a | (b << 8));
+                if (keep) ring[(rc + __popcll(mk & below)) & (RING - 1)] = (uint16_t)(a | (b << 8));
                 rc += (unsigned)__popcll(mk);
-                if (rc - rd >= 64) {
-                    wave_lds_sync();
-                    test_batch(64);
-                }
             }
-            if (rc > rd) {
-                wave_lds_sync();
-                test_batch(rc - rd);
+            if (g == hit_row) {
+                wave_lds_sync();  // LDS reads of this tile pair before the next staging
+                continue;
             }
-            n_tested += rc;
             if (MODE == 0) {
                 const Tt dm = wave_min(tmin);
                 if (PREC == 0) {
@@ -2673,17 +2835,16 @@ __global__ __launch_bounds__(64) void k_pairs(const float *t32A, const double *t
                 }
             }
             wave_lds_sync();  // LDS reads of this tile pair before the next staging
-            i = nx;
         }
         if (MODE == 0 && L.log) {
             // entries pruned at dequeue: their box bound is the logged
             // (lower-bound) outcome
             for (int k = 0; k < bn; k++)
-                if (rl_i(E.ta, k) >= 0 && !rl_i(E.hit, k) && !live(k) &&
-                    (L.seed_pass || (int)(q0 + (unsigned)k) != rl_i(E.seed_q, k)) && lane == 0) {
-                    const int kg = rl_i(E.g, k);
-                    log_tile_pair(L, mA[rl_i(E.ta, k)], mB[rl_i(E.tb, k)], rows[kg].scale, rl_f(E.lbf, k),
-                                  rl_f(E.lbf, k), kg);
+                if (ents[k].ta >= 0 && !ents[k].hit && !((live >> k) & 1ull) &&
+                    (L.seed_pass || (int)(q0 + (unsigned)k) != uni(ents[k].seed_q)) && lane == 0) {
+                    const int kg = uni(ents[k].g);
+                    log_tile_pair(L, mA[uni(ents[k].ta)], mB[uni(ents[k].tb)], rows[kg].scale, uni(ents[k].lbf),
+                                  uni(ents[k].lbf), kg);
                 }
         }
         claim = (unsigned)__builtin_amdgcn_readfirstlane((int)nxt);

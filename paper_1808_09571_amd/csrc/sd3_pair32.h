@@ -159,11 +159,12 @@ __device__ __forceinline__ float orient3d_f32(float ax, float ay, float az, floa
 // products is at most Ms^3 and passes through at most 8 FP32 roundings
 // (48 u Ms^3 < 64 u Ms^3), and moving the 4 points by at most eps each moves
 // the determinant by at most 18 eps Ms^2 + O(eps^2 Ms).
-__device__ __forceinline__ int isect32(TriRef<float> A, TriRef<float> B, float eps_c) {
+// A, B: the corners (9 values); xA, xB: the boxes (lo xyz, hi xyz).
+__device__ __forceinline__ int isect32(const float *A, const float *B, const float *xA, const float *xB,
+                                       float eps_c) {
     float ms = 0.0f;
 #pragma unroll
-    for (int k = 0; k < 3; k++)
-        ms = fmaxf(ms, fmaxf(A[F_HI + k], B[F_HI + k]) - fminf(A[F_LO + k], B[F_LO + k]));
+    for (int k = 0; k < 3; k++) ms = fmaxf(ms, fmaxf(xA[3 + k], xB[3 + k]) - fminf(xA[k], xB[k]));
     ms *= 1.0f + 0x1p-20f;
     const float eo = (24.0f * eps_c * ms * ms + 24.0f * eps_c * eps_c * ms +
                       8.0f * eps_c * eps_c * eps_c + 64.0f * 0x1p-24f * ms * ms * ms) *
@@ -171,8 +172,7 @@ __device__ __forceinline__ int isect32(TriRef<float> A, TriRef<float> B, float e
     float o[2][3];
 #pragma unroll
     for (int side = 0; side < 2; side++) {
-        TriRef<float> P = side ? B : A;
-        TriRef<float> T = side ? A : B;
+        const float *P = side ? B : A, *T = side ? A : B;
 #pragma unroll
         for (int i = 0; i < 3; i++)
             o[side][i] = orient3d_f32(T[0], T[1], T[2], T[3], T[4], T[5], T[6], T[7], T[8],
@@ -183,8 +183,7 @@ __device__ __forceinline__ int isect32(TriRef<float> A, TriRef<float> B, float e
     }
 #pragma unroll
     for (int side = 0; side < 2; side++) {
-        TriRef<float> P = side ? B : A;
-        TriRef<float> T = side ? A : B;
+        const float *P = side ? B : A, *T = side ? A : B;
 #pragma unroll
         for (int i = 0; i < 3; i++) {
             int j = (i + 1) % 3;
