@@ -84,7 +84,9 @@ typedef struct sd3_geoms {
 /*
  * Seed round of sd3_distance (results never depend on it): before the main
  * pass, each row's best-ranked candidate tile pair is evaluated, so that its
- * distance tightens the upper bound used to prune the others.
+ * distance tightens the upper bound used to prune the others.  A queue short
+ * enough that every candidate is taken up at once has none (there is nothing
+ * left to prune).
  */
 #define SD3_ORDER_BOUND 0   /* rank by bounding-box lower bound (default) */
 #define SD3_ORDER_NONE 1    /* no seed round */

@@ -608,6 +608,7 @@ void plan_call(sd3_ctx *ctx, Workspace &ws, const sd3_geoms *a, const sd3_geoms 
     int &gp = ctx->pairs_grid[prec][mode][tk_index(tk)];
     if (gp == 0) gp = ctx->cus * pairs_blocks_per_cu(prec, mode, tk);
     C.grid_pairs = gp;
+    L.seed_min = (unsigned int)gp;
     // the queue holds at most qcap tile pairs: split the work items into
     // passes whose potential tile pairs fit
     C.n_wi = P.wi[G];

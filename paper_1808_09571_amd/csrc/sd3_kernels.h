@@ -134,6 +134,7 @@ struct Lists {
     unsigned int *xcount;
     unsigned int xcap;
     unsigned long long *counters;  // [C_NCOUNTERS]
+    unsigned int seed_min;         // a queue of at most this many entries has no seed round
     int seed_pass;                 // 1: entries are the rows' seed choices (RowState::best)
     int64_t nrows;                 // rows (entries of a seed pass)
     float *log;                    // training log (device) or nullptr

@@ -2402,6 +2402,11 @@ __global__ __launch_bounds__(64, PREC == 0 && TK <= 64 ? 3 : 1) void k_pairs(con
     const int lane = lane_id();
     const unsigned long long below = lanes_below();
     const unsigned qcount = L.seed_pass ? (unsigned)L.nrows : min(*L.qcount, L.qcap);
+    // a queue whose every entry has a wave of its own at once has no seed
+    // round: a bound known earlier could prune nothing that still waits (the
+    // ranking and the round cost the 512 x 512-cell TIN pair 24 us of 208, an
+    // icosphere pair 13 of 141)
+    if (L.seed_pass && min(*L.qcount, L.qcap) <= L.seed_min) return;
     const unsigned nwave = gridDim.x;
     // entries per claim: 1 for short queues (every wave starts at once), up
     // to QB for long ones (one atomic and one gather per batch)
@@ -3242,7 +3247,8 @@ __global__ __launch_bounds__(256) void k_rank(const TileMeta *mA, const TileMeta
     __shared__ MlpWave Wv[4];
     const unsigned n = min(*L.qcount, L.qcap);
     const unsigned nw = gridDim.x * 4u;
-    if ((unsigned)blockIdx.x * 64u >= n) return;  // no pair for this block: skip the weights
+    // (no pair for this block, or no seed round: skip the weights)
+    if ((unsigned)blockIdx.x * 64u >= n || n <= L.seed_min) return;
     mlp_stage(M, W);
     __syncthreads();
     const int lane = lane_id(), wv = threadIdx.x >> 6;
