@@ -182,9 +182,11 @@ constexpr int64_t CULL_MIN_ROWS = 64;              // pre-cull of large sorts ab
 constexpr int64_t COMPACT_MIN_ROWS = 64;           // compacted work lists above this
 // device scalars: [0] queue count [1] queue head [2] rescue count [3] rescue
 // head [4] exact count [7] seed pass head [8] [9] work-item counts [11] exact
-// blocks done [12] [13] validation flags of a and b; the counters follow at
-// byte 64
-constexpr size_t SCALAR_BYTES = 64 + sizeof(unsigned long long) * C_NCOUNTERS;
+// blocks done [12] [13] validation flags of a and b; the counters' replicas
+// follow at byte 64
+constexpr size_t SCALAR_BYTES = 64 + sizeof(unsigned long long) * C_REPLICAS * C_NCOUNTERS;
+constexpr size_t RESULT_BYTES = 64 + sizeof(unsigned long long) * C_NCOUNTERS;  // the scalars and replica 0
+constexpr size_t READBACK_BYTES = (SCALAR_BYTES + 511) / 512 * 512;
 
 struct HipError {
     hipError_t e;
@@ -217,27 +219,27 @@ void *ensure(DevBuf &b, size_t bytes) {
     return b.p;
 }
 
-// Pinned host staging of `bytes` (+ a 512-byte readback area at the end).
+// Pinned host staging of `bytes` (+ a readback area at the end).
 char *ensure_pinned(sd3_ctx *ctx, size_t bytes) {
-    bytes += 512;
+    bytes += READBACK_BYTES;
     if (ctx->pin_cap < bytes) {
         if (ctx->pin) check(hipHostFree(ctx->pin), "hipHostFree");
         ctx->pin = nullptr;
         ctx->pin_cap = 0;
-        size_t want = bytes + bytes / 4 + 4096;
+        size_t want = (bytes + bytes / 4 + 4096) / 512 * 512;
         check(hipHostMalloc(&ctx->pin, want, hipHostMallocDefault), "hipHostMalloc");
         ctx->pin_cap = want;
     }
     return (char *)ctx->pin;
 }
 
-char *readback_area(sd3_ctx *ctx) { return (char *)ctx->pin + ctx->pin_cap - 512; }
+char *readback_area(sd3_ctx *ctx) { return (char *)ctx->pin + ctx->pin_cap - READBACK_BYTES; }
 
 // Pinned staging for a call on workspace `ws`: an allocation-free call only
 // uses what the context allocated at creation (its row limit keeps `bytes`
 // within it).
 char *staging(sd3_ctx *ctx, const Workspace &ws, size_t bytes) {
-    if (ws.arena && bytes + 512 > ctx->pin_cap) throw HipError{hipErrorOutOfMemory, "static host staging"};
+    if (ws.arena && bytes + READBACK_BYTES > ctx->pin_cap) throw HipError{hipErrorOutOfMemory, "static host staging"};
     return ensure_pinned(ctx, bytes);
 }
 
@@ -849,7 +851,7 @@ sd3_status run(sd3_ctx *ctx, Workspace &ws, const sd3_geoms *a, const sd3_geoms 
         char *rb = readback_area(ctx);
         const unsigned int *sc_h = (const unsigned int *)rb;
         const unsigned long long *cnt_h = (const unsigned long long *)(rb + 64);
-        alignas(16) char rbcopy[SCALAR_BYTES];
+        alignas(16) char rbcopy[RESULT_BYTES];
         // device inputs are validated by the call's kernels (coordinates
         // first, indices by the key kernel); the flags are read with the
         // counters at the end, and a flagged call writes no result
@@ -869,7 +871,7 @@ sd3_status run(sd3_ctx *ctx, Workspace &ws, const sd3_geoms *a, const sd3_geoms 
         if (a->mem == SD3_MEM_DEVICE) clk.mark(7);
         // scalars and counters: an error leaves the outputs untouched (the
         // final kernel did not write them)
-        check(hipMemcpyAsync(rb, C.sc, SCALAR_BYTES, hipMemcpyDeviceToHost, s), "D2H counters");
+        check(hipMemcpyAsync(rb, C.sc, RESULT_BYTES, hipMemcpyDeviceToHost, s), "D2H counters");
         check(hipStreamSynchronize(s), "sync");
         check(hipGetLastError(), "kernel launch");
         st = flags_status(ctx, sc_h);
@@ -879,7 +881,7 @@ sd3_status run(sd3_ctx *ctx, Workspace &ws, const sd3_geoms *a, const sd3_geoms 
         if (ovf == OVF_NONE && opts.semantics == SD3_SOLID) {
             // the staging below may move the pinned buffer the scalars were
             // read into: keep a copy of them
-            memcpy(rbcopy, rb, SCALAR_BYTES);
+            memcpy(rbcopy, rb, RESULT_BYTES);
             sc_h = (const unsigned int *)rbcopy;
             cnt_h = (const unsigned long long *)(rbcopy + 64);
             const size_t hb = (size_t)C.P.G * 12 + 64;
@@ -1168,8 +1170,11 @@ sd3_status sd3_segments(sd3_ctx *ctx, int32_t op, const double *seg, int64_t n, 
         if (f & V_NONFINITE) return fail(ctx, SD3_E_NONFINITE, "non-finite coordinate");
         if (f & V_RANGE) return fail(ctx, SD3_E_RANGE, "coordinate magnitude outside [2^-256, 2^256]");
         if (f & V_INDEX) return fail(ctx, SD3_E_INDEX_RANGE, "triangle index outside the mesh");
-        const unsigned long long *cnt_h = (const unsigned long long *)(rb + 64);
         if (stats) {
+            unsigned long long cnt_h[3] = {};
+            for (int c = 0; c < 3; c++)
+                for (int r = 0; r < C_REPLICAS; r++)
+                    cnt_h[c] += ((const unsigned long long *)(rb + 64))[r * C_NCOUNTERS + c];
             memset(stats, 0, sizeof(*stats));
             stats->tile_pairs_total = ntiles * ((n + 63) / 64);
             stats->tri_pairs_boxed = (int64_t)cnt_h[0];
@@ -1288,7 +1293,7 @@ sd3_status sd3_graph_create(sd3_ctx *ctx, int32_t kind, const sd3_geoms *a, cons
     try {
         check(hipSetDevice(ctx->device), "hipSetDevice");
         check(hipStreamCreateWithFlags(&g->cs, hipStreamNonBlocking), "hipStreamCreate");
-        check(hipHostMalloc(&g->pin, SCALAR_BYTES, hipHostMallocDefault), "hipHostMalloc");
+        check(hipHostMalloc(&g->pin, RESULT_BYTES, hipHostMallocDefault), "hipHostMalloc");
         plan_call(ctx, g->ws, a, b, opts, mode, tk, dist, hit, g->C, g->cs);
         // validate the current contents once, before anything reads them
         enqueue_validate(g->C, g->cs, true);
@@ -1347,7 +1352,7 @@ sd3_status sd3_graph_result(sd3_graph *g, sd3_stats *stats, void *stream) {
     try {
         check(hipSetDevice(ctx->device), "hipSetDevice");
         hipStream_t s = (hipStream_t)stream;
-        check(hipMemcpyAsync(g->pin, g->C.sc, SCALAR_BYTES, hipMemcpyDeviceToHost, s), "D2H counters");
+        check(hipMemcpyAsync(g->pin, g->C.sc, RESULT_BYTES, hipMemcpyDeviceToHost, s), "D2H counters");
         check(hipStreamSynchronize(s), "sync");
     } catch (const HipError &e) {
         return device_error(ctx, e);

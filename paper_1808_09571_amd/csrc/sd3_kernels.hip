@@ -8,7 +8,7 @@
 #include "sd3_pair32.h"
 #include "sd3_exact.h"
 
-static_assert(sd3::C_NCOUNTERS <= 256, "the first block clears every counter");
+static_assert(sd3::C_REPLICAS * sd3::C_NCOUNTERS <= 512, "the first two blocks clear every counter");
 
 namespace sd3 {
 
@@ -167,7 +167,7 @@ __global__ void k_prep_init(unsigned int *sc, uint32_t *flags, unsigned long lon
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i < 12) sc[i] = 0u;
     if (i < 2) flags[i] = 0u;
-    if (i < C_NCOUNTERS) counters[i] = 0ull;
+    if (i < C_REPLICAS * C_NCOUNTERS) counters[i] = 0ull;
     if (i < nbox) {
         unsigned long long v = (i % 6) < 3 ? ~0ull : 0ull;
         boxA[i] = v;
@@ -372,8 +372,7 @@ void launch_validate_rowbox(SideBufs &A, SideBufs &B, PrepBufs &P, uint32_t *fla
     const int64_t G = A.G;
     const int64_t nbox = (int64_t)A.boxrep * G * 6;
     const int64_t nkc = P.kc ? 2 * G : 0;
-    // (one block at least: C_NCOUNTERS <= 256)
-    const int64_t nz = std::max<int64_t>(256, std::max(nbox, nkc));
+    const int64_t nz = std::max<int64_t>(C_REPLICAS * C_NCOUNTERS, std::max(nbox, nkc));
     hipLaunchKernelGGL(k_prep_init, dim3(grid_for(nz, 256)), dim3(256), 0, s, L.qcount, flags, L.counters,
                        A.rowbox, B.rowbox, nbox, P.kc, nkc);
     XyzSide xa{A.xyz, A.nv, A.v_off, A.rowbox, rowbox_blocks(A.nv), A.boxrep};
@@ -1641,7 +1640,7 @@ __global__ __launch_bounds__(256) void k_materialize(MatSide A, MatSide B, Lists
         const bool cb = tb >= 0 && B.mat[tb] == 0u && atomicExch(&B.mat[tb], 1u) == 0u;
         unsigned long long ma = __ballot(ca), mb = __ballot(cb);
         if ((ma | mb) && lane == 0)
-            atomicAdd(&L.counters[C_COPIED], (unsigned long long)(__popcll(ma) + __popcll(mb)));
+            atomicAdd(counter_of(L.counters, C_COPIED), (unsigned long long)(__popcll(ma) + __popcll(mb)));
         while (ma) mat_group<PREC, TK, NG>(A, ma, ta);
         while (mb) mat_group<PREC, TK, NG>(B, mb, tb);
     }
@@ -1961,47 +1960,53 @@ __global__ __launch_bounds__(256) void k_filter(const TileMeta *mA, const TileMe
     double lim2 = lim * lim * (1.0 + 32.0 * U64);
     bool hit = R.hit != 0;
     unsigned long long best = ~0ull;  // this wave's seed candidate
-    // groups of FG A tiles share one queue claim (their entries keep the
-    // per-tile order, a-major then lane)
-    constexpr int FG = 8;
-    for (int a0 = 0; a0 < w.na; a0 += FG) {
-        float lbf[FG];
+    // the wave's kept pairs (bit a of a lane: A tile a) are counted first and
+    // share one queue claim: the claims of a call all go to one address, one
+    // after the other (4096 rows: 359 -> 188 us; a claim per 8 A tiles before)
+    unsigned long long keeps = 0, any = 0;
+    unsigned int tot = 0;
+    constexpr int FG = 8;  // A tiles in flight
+    for (int a0 = 0; a0 < w.na && !hit; a0 += FG) {
         unsigned long long m[FG];
-        unsigned int tot = 0;
 #pragma unroll
         for (int j = 0; j < FG; j++) {
             const int a = a0 + j;
             bool keep = false;
-            lbf[j] = 0.0f;
-            if (a < w.na && w.bvalid && !hit) {
-                double g2 = box_gap2(box[a], box[a] + 3, blo, bhi);
-                if (mode == 0) {
-                    keep = g2 <= lim2;
-                    if (keep) lbf[j] = (float)(sqrt(g2) * (1.0 - 8.0 * U64) * (1.0 - 0x1p-20));
-                } else {
-                    keep = g2 == 0.0 && box[a][0] <= bhi[0] && blo[0] <= box[a][3] &&
-                           box[a][1] <= bhi[1] && blo[1] <= box[a][4] && box[a][2] <= bhi[2] &&
-                           blo[2] <= box[a][5];
-                }
+            if (a < w.na && w.bvalid) {
+                const double g2 = box_gap2(box[a], box[a] + 3, blo, bhi);
+                keep = mode == 0 ? g2 <= lim2
+                                 : g2 == 0.0 && box[a][0] <= bhi[0] && blo[0] <= box[a][3] && box[a][1] <= bhi[1] &&
+                                       blo[1] <= box[a][4] && box[a][2] <= bhi[2] && blo[2] <= box[a][5];
             }
             m[j] = __ballot(keep);
-            tot += (unsigned int)__popcll(m[j]);
         }
-        if (tot == 0) continue;
+#pragma unroll
+        for (int j = 0; j < FG; j++)
+            if (m[j]) {
+                any |= 1ull << (a0 + j);
+                tot += (unsigned int)__popcll(m[j]);
+                keeps |= ((m[j] >> lane_id()) & 1ull) << (a0 + j);
+            }
+    }
+    if (tot) {
         unsigned int basei = 0;
         if (lane_id() == 0) basei = atomicAdd(qcount, tot);
         basei = __builtin_amdgcn_readfirstlane(basei);
-#pragma unroll
-        for (int j = 0; j < FG; j++) {
-            const bool keep = (m[j] >> lane_id()) & 1ull;
-            const unsigned int idx = basei + (unsigned int)__popcll(m[j] & lanes_below());
-            basei += (unsigned int)__popcll(m[j]);
+        // entries in A-tile order, then by lane
+        for (; any; any &= any - 1) {
+            const int a = __ffsll((long long)any) - 1;
+            const bool keep = (keeps >> a) & 1ull;
+            const unsigned long long m = __ballot(keep);
+            const unsigned int idx = basei + (unsigned int)__popcll(m & lanes_below());
+            basei += (unsigned int)__popcll(m);
             if (keep && idx < qcap) {
-                queue[idx] = make_int2((int)(w.a0 + a0 + j), (int)w.b);
-                qlb[idx] = lbf[j];
+                float lbf = 0.0f;
+                if (mode == 0)
+                    lbf = (float)(sqrt(box_gap2(box[a], box[a] + 3, blo, bhi)) * (1.0 - 8.0 * U64) * (1.0 - 0x1p-20));
+                queue[idx] = make_int2((int)(w.a0 + a), (int)w.b);
+                qlb[idx] = lbf;
+                if (RANK == 1) best = min(best, ((unsigned long long)float_order_bits(lbf) << 32) | idx);
             }
-            if (RANK == 1 && keep && idx < qcap)
-                best = min(best, ((unsigned long long)float_order_bits(lbf[j]) << 32) | idx);
         }
     }
     if (RANK == 1) {
@@ -2496,6 +2501,7 @@ __global__ __launch_bounds__(64, PREC == 0 && TK <= 64 ? 3 : 1) void k_pairs(con
             // the row bound now: the batch's, or the one read with the tiles
             double ub = uni(e.ub);
             if (MODE == 0) ub = fmin(ub, bits_to_double(rl_u64(raw_ub, 0)));
+            const double ub0 = ub;  // (a bound no lower is not sent)
             // cull thresholds of the row bound (see sd3_pair32.h for eps_c)
             float T2f = 0.0f, limf = 0.0f;
             double T2d = 0.0;
@@ -2821,7 +2827,7 @@ __global__ __launch_bounds__(64, PREC == 0 && TK <= 64 ? 3 : 1) void k_pairs(con
                     double ub_now = ub;
                     if ((float)dm < __builtin_inff()) {
                         const double U = fp32_upper((float)dm, eu);
-                        if (lane == 0) atomicMin(&rows[g].ub, double_to_bits(U));
+                        if (lane == 0 && U < ub0) atomicMin(&rows[g].ub, double_to_bits(U));
                         ub_now = fmin(ub_now, U);
                     }
                     const double lim = ub_now + msc + 1.4551915228366852e-11 * ub_now;
@@ -2829,7 +2835,7 @@ __global__ __launch_bounds__(64, PREC == 0 && TK <= 64 ? 3 : 1) void k_pairs(con
                     rescue_tested(lim);
                 } else if (lane == 0 && (double)dm < __builtin_inf()) {
                     atomic_min_pos(&rows[g].d2, (double)dm);
-                    atomic_min_pos(&rows[g].ub, sqrt((double)dm));
+                    if (sqrt((double)dm) < ub0) atomic_min_pos(&rows[g].ub, sqrt((double)dm));
                 }
                 if (L.log && lane == 0) {
                     // smallest tested candidate distance, else the cull
@@ -2859,12 +2865,12 @@ __global__ __launch_bounds__(64, PREC == 0 && TK <= 64 ? 3 : 1) void k_pairs(con
     n_exact = wave_sum(n_exact);
     n_bad = wave_sum(n_bad);
     if (lane == 0) {
-        if (n_eval) atomicAdd(&L.counters[C_TP_EVAL], n_eval);
-        if (n_boxed) atomicAdd(&L.counters[C_TRI_BOXED], n_boxed);
-        if (n_tested) atomicAdd(&L.counters[PREC == 0 ? C_TRI32 : C_TRI64], n_tested);
-        if (n_resc) atomicAdd(&L.counters[C_RESCUED], n_resc);
-        if (n_exact) atomicAdd(&L.counters[C_EXACT], n_exact);
-        if (n_bad) atomicAdd(&L.counters[C_SKEW], n_bad);
+        if (n_eval) atomicAdd(counter_of(L.counters, C_TP_EVAL), n_eval);
+        if (n_boxed) atomicAdd(counter_of(L.counters, C_TRI_BOXED), n_boxed);
+        if (n_tested) atomicAdd(counter_of(L.counters, PREC == 0 ? C_TRI32 : C_TRI64), n_tested);
+        if (n_resc) atomicAdd(counter_of(L.counters, C_RESCUED), n_resc);
+        if (n_exact) atomicAdd(counter_of(L.counters, C_EXACT), n_exact);
+        if (n_bad) atomicAdd(counter_of(L.counters, C_SKEW), n_bad);
     }
 }
 
@@ -2996,8 +3002,8 @@ __device__ void rescue_items(const TriSrc &SA, const TriSrc &SB, RowState *rows,
     n64 = wave_sum(n64);
     nex = wave_sum(nex);
     if (lane_id() == 0) {
-        if (n64) atomicAdd(&L.counters[C_TRI64], n64);
-        if (nex) atomicAdd(&L.counters[C_EXACT], nex);
+        if (n64) atomicAdd(counter_of(L.counters, C_TRI64), n64);
+        if (nex) atomicAdd(counter_of(L.counters, C_EXACT), nex);
     }
 }
 
@@ -3059,6 +3065,18 @@ __device__ __forceinline__ bool last_block_done(unsigned int *done) {
     return last != 0;
 }
 
+// Adds the counters' replicas into replica 0, which the host reads (the last
+// block of the call's last counting kernel; its last threads, one per counter:
+// in a block of several waves not the wave that writes the first rows).
+__device__ __forceinline__ void sum_counters(const Lists &L) {
+    const int c = (int)(blockDim.x - 1 - threadIdx.x);
+    if (c >= C_NCOUNTERS) return;
+    unsigned long long s = 0;
+#pragma unroll
+    for (int r = 0; r < C_REPLICAS; r++) s += load_acq(&L.counters[r * C_NCOUNTERS + c]);
+    L.counters[c] = s;
+}
+
 // The results of rows [0, fin_rows), unless the call failed on the device.
 __device__ __forceinline__ void finalize_rows(const RowState *rows, int64_t fin_rows, double *dist,
                                               uint8_t *hit, const Lists &L, const uint32_t *vflags) {
@@ -3071,8 +3089,9 @@ __global__ __launch_bounds__(64) void k_exact(TriSrc SA, TriSrc SB, RowState *ro
                                               int mode, int64_t fin_rows, double *dist,
                                               uint8_t *hit, const uint32_t *vflags) {
     exact_items(SA, SB, rows, L, mode, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
-    if (fin_rows <= 0) return;
-    if (last_block_done(L.xdone)) finalize_rows(rows, fin_rows, dist, hit, L, vflags);
+    if (!last_block_done(L.xdone)) return;
+    sum_counters(L);
+    if (fin_rows > 0) finalize_rows(rows, fin_rows, dist, hit, L, vflags);
 }
 
 void launch_exact(const SideBufs &A, const SideBufs &B, RowState *rows, Lists &L, int mode,
@@ -3092,6 +3111,7 @@ __global__ __launch_bounds__(256) void k_resolve(TriSrc SA, TriSrc SB, RowState 
     rescue_items<MODE>(SA, SB, rows, L, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
     if (!last_block_done(L.xdone)) return;
     exact_items(SA, SB, rows, L, MODE, threadIdx.x, blockDim.x);
+    sum_counters(L);
     if (fin_rows > 0) {
         // this block's own exact updates, then fresh row states
         __syncthreads();

@@ -371,7 +371,7 @@ __device__ __forceinline__ void lds_sync() {
 
 // MODE 0: distance (dist[i], hit[i] optional); 1: intersects (hit[i]);
 // 2: within r (hit[i] = distance <= r).  cnt[0..2]: triangle bounds compared,
-// full pair tests, exact tests (summed per wave).
+// full pair tests, exact tests (summed per wave, in replicas).
 template <int MODE>
 __global__ __launch_bounds__(64, 3) void k_segs(const double *seg, int64_t n, const double *P, int64_t nt,
                                              const float4 *nodes, SegTree T, const unsigned long long *box,
@@ -614,16 +614,16 @@ __global__ __launch_bounds__(64, 3) void k_segs(const double *seg, int64_t n, co
     const unsigned long long tb = wave_sum((unsigned long long)n_box), tf = wave_sum((unsigned long long)n_full),
                              te = wave_sum((unsigned long long)n_ex);
     if (lane == 0) {
-        if (tb) atomicAdd(&cnt[0], tb);
-        if (tf) atomicAdd(&cnt[1], tf);
-        if (te) atomicAdd(&cnt[2], te);
+        if (tb) atomicAdd(counter_of(cnt, 0), tb);
+        if (tf) atomicAdd(counter_of(cnt, 1), tf);
+        if (te) atomicAdd(counter_of(cnt, 2), te);
     }
 }
 
 // Flags and counters to 0, the mesh box to the empty one.
 __global__ void k_seg_clear(uint32_t *flags, unsigned long long *cnt, unsigned long long *box) {
     if (threadIdx.x < 2) flags[threadIdx.x] = 0;
-    if (threadIdx.x < 4) cnt[threadIdx.x] = 0;
+    if (threadIdx.x < C_REPLICAS * C_NCOUNTERS) cnt[threadIdx.x] = 0;
     if (threadIdx.x < 6) box[threadIdx.x] = threadIdx.x < 3 ? ~0ull : 0ull;
 }
 
@@ -648,7 +648,7 @@ SegTree seg_tree(int64_t nt) {
 void launch_seg_validate(const double *seg, int64_t n, const double *xyz, int64_t nv, const int32_t *tri,
                          int64_t nt, uint32_t *flags, unsigned long long *cnt, unsigned long long *box,
                          hipStream_t s) {
-    hipLaunchKernelGGL(k_seg_clear, dim3(1), dim3(64), 0, s, flags, cnt, box);
+    hipLaunchKernelGGL(k_seg_clear, dim3(1), dim3(C_REPLICAS * C_NCOUNTERS), 0, s, flags, cnt, box);
     const int64_t work = std::max<int64_t>(6 * n, std::max<int64_t>(3 * nv, 3 * nt));
     const unsigned grid = (unsigned)std::min<int64_t>(std::max<int64_t>((work + 255) / 256, 1), 4096);
     hipLaunchKernelGGL(k_seg_validate, dim3(grid), dim3(256), 0, s, seg, n, xyz, nv, tri, nt, flags, box);
