@@ -917,8 +917,8 @@ __global__ __launch_bounds__(64) void k_scan_top(uint32_t *part, int64_t n) {
     }
 }
 
-// Stable scatter of one radix pass.  Wave w of a block ranks the block's
-// quarter [w*Q, (w+1)*Q) in rounds of 64 items (8 ballots find the lanes with
+// Stable scatter of one radix pass.  Wave w of a block ranks a quarter of the
+// block's items, in rounds of 64 (8 ballots find the lanes with
 // the same digit); per-wave running digit counts live in LDS, so ranking
 // needs no block-wide barrier.  The block then places its items in LDS in
 // digit order and writes each digit's run to consecutive global addresses.
@@ -928,14 +928,13 @@ __global__ __launch_bounds__(64) void k_scan_top(uint32_t *part, int64_t n) {
 // pass's keys, which nothing reads, are not written); MODE 1: key and value
 // in, one word out (the next digit above the 24-bit value); MODE 2: words in
 // and out (the digit is the top byte).
-template <int RS_ITEMS, int MODE>
+template <int RS_ITEMS, int MODE, bool PART>
 __global__ __launch_bounds__(256) void k_scatter(const uint32_t *kin, const int32_t *vin, uint32_t *kout,
                                                  int32_t *vout, SortSeg S, int shift,
                                                  const uint32_t *hist, const uint32_t *part, int ncraw,
                                                  int later) {
     using KT = uint32_t;
-    constexpr int Q = RS_ITEMS / 4;   // items per wave
-    constexpr int R = Q / 64;         // rounds per wave
+    constexpr int R = RS_ITEMS / 256;  // most rounds of a wave
     __shared__ uint32_t wc[4][256];   // per-wave digit counts, then per-wave offsets
     __shared__ uint32_t gbase[256];   // global position of the block's first item of each digit
     __shared__ uint32_t loff[256];    // block-local position of each digit's first item
@@ -953,8 +952,14 @@ __global__ __launch_bounds__(256) void k_scatter(const uint32_t *kin, const int3
     // (first in the block for the first pass, first in the row after it; the
     // culled ones keep their reserved places, digit 255 at the row's end,
     // unwritten)
-    const int nvalid = later ? kept_in_block(S, sbk) : (S.bn ? S.bn[blk] : sbk.n);
-    const int64_t n = b0 + nvalid;
+    const int nvalid = !PART ? sbk.n : later ? kept_in_block(S, sbk) : S.bn[blk];
+    if (PART && nvalid <= 0) return;  // (block-uniform)
+    // the ranking is what this kernel is bound by (vector instructions, 94% of
+    // its cycles on a culled column of 43M triangles): in a culling call (PART)
+    // the waves take even shares of the items that are there, in whole rounds
+    // (intersects over 1000 rows: passes 107 + 104 -> 53 + 44 us; distance over
+    // 4096: 430 + 404 -> 297 + 227); blocks are full otherwise
+    const int rq = PART ? (nvalid + 255) / 256 : R;  // rounds per wave
     if (ncraw > 0) {
         // exclusive scan of the raw chunk totals (one per thread) into loff
         __shared__ uint32_t csum[4];
@@ -981,25 +986,30 @@ __global__ __launch_bounds__(256) void k_scatter(const uint32_t *kin, const int3
     // issue every load of this thread before ranking (one memory latency)
 #pragma unroll
     for (int r = 0; r < R; r++) {
-        int64_t i = b0 + w * Q + r * 64 + lane;
-        key[r] = i < n ? kin[i] : (KT)0;
-        if (V) val[r] = i < n ? vin[i] : 0;
+        const int j = (w * rq + r) * 64 + lane;
+        const bool valid = r < rq && j < nvalid;
+        key[r] = valid ? kin[b0 + j] : (KT)0;
+        if (V) val[r] = valid ? vin[b0 + j] : 0;
+        rk[r] = 0xffffffffu;
     }
+#pragma unroll
     for (int r = 0; r < R; r++) {
-        int64_t i = b0 + w * Q + r * 64 + lane;
-        bool valid = i < n;
-        uint32_t d = (uint32_t)((key[r] >> shift) & 255);
-        unsigned long long peers = __ballot(valid);
-        for (int bit = 0; bit < 8; bit++) {
-            unsigned long long m = __ballot((d >> bit) & 1u);
-            peers &= ((d >> bit) & 1u) ? m : ~m;
+        if (r < rq) {  // (block-uniform)
+            const bool valid = (w * rq + r) * 64 + lane < nvalid;
+            uint32_t d = (uint32_t)((key[r] >> shift) & 255);
+            unsigned long long peers = __ballot(valid);
+#pragma unroll
+            for (int bit = 0; bit < 8; bit++) {
+                unsigned long long m = __ballot((d >> bit) & 1u);
+                peers &= ((d >> bit) & 1u) ? m : ~m;
+            }
+            uint32_t before = valid ? wc[w][d] : 0u;
+            __builtin_amdgcn_wave_barrier();
+            uint32_t rank = (uint32_t)__popcll(peers & lanes_below());
+            rk[r] = valid ? before + rank : 0xffffffffu;
+            if (valid && rank == 0) wc[w][d] = before + (uint32_t)__popcll(peers);
+            __builtin_amdgcn_wave_barrier();
         }
-        uint32_t before = valid ? wc[w][d] : 0u;
-        __builtin_amdgcn_wave_barrier();
-        uint32_t rank = (uint32_t)__popcll(peers & lanes_below());
-        rk[r] = valid ? before + rank : 0xffffffffu;
-        if (valid && rank == 0) wc[w][d] = before + (uint32_t)__popcll(peers);
-        __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
     // digit totals -> block-local offsets (thread = digit), then per-wave offsets
@@ -1019,8 +1029,9 @@ __global__ __launch_bounds__(256) void k_scatter(const uint32_t *kin, const int3
         wc[3][tid] = pre + c0 + c1 + c2;
     }
     __syncthreads();
+#pragma unroll
     for (int r = 0; r < R; r++) {
-        if (rk[r] == 0xffffffffu) continue;
+        if (r >= rq || rk[r] == 0xffffffffu) continue;
         uint32_t d = (uint32_t)((key[r] >> shift) & 255);
         uint32_t slot = wc[w][d] + rk[r];
         if (MODE == 1) {
@@ -1048,7 +1059,7 @@ __global__ __launch_bounds__(256) void k_scatter(const uint32_t *kin, const int3
 // Sort (keys[0], vals[0]) within rows by K's key bits; result in keys[res]
 // (narrow sorts: words) or vals[res].  The first pass's histogram is already
 // in `hist` (from the key kernel).
-template <int RS_ITEMS>
+template <int RS_ITEMS, bool PART>
 static int radix_sort(uint32_t **keys, int32_t **vals, uint32_t *hist, uint32_t *part, const SortSeg &S,
                       const SortKey &K, hipStream_t s, KernelEvents *kev) {
     int cur = 0;
@@ -1070,13 +1081,13 @@ static int radix_sort(uint32_t **keys, int32_t **vals, uint32_t *hist, uint32_t 
         const int ncr = inline_top ? nchunk : 0;
         const int later = p > 0 ? 1 : 0;
         if (mode == 2)
-            hipLaunchKernelGGL((k_scatter<RS_ITEMS, 2>), dim3(nb), dim3(256), 0, s, keys[cur], nullptr,
+            hipLaunchKernelGGL((k_scatter<RS_ITEMS, 2, PART>), dim3(nb), dim3(256), 0, s, keys[cur], nullptr,
                                keys[cur ^ 1], nullptr, S, shift, hist, part, ncr, later);
         else if (mode == 1)
-            hipLaunchKernelGGL((k_scatter<RS_ITEMS, 1>), dim3(nb), dim3(256), 0, s, keys[cur], vals[cur],
+            hipLaunchKernelGGL((k_scatter<RS_ITEMS, 1, PART>), dim3(nb), dim3(256), 0, s, keys[cur], vals[cur],
                                keys[cur ^ 1], nullptr, S, shift, hist, part, ncr, later);
         else
-            hipLaunchKernelGGL((k_scatter<RS_ITEMS, 0>), dim3(nb), dim3(256), 0, s, keys[cur], vals[cur],
+            hipLaunchKernelGGL((k_scatter<RS_ITEMS, 0, PART>), dim3(nb), dim3(256), 0, s, keys[cur], vals[cur],
                                last ? nullptr : keys[cur ^ 1], vals[cur ^ 1], S, shift, hist, part, ncr, later);
         if (kev) kev->end(KE_SCATTER, s);
         cur ^= 1;
@@ -1492,7 +1503,10 @@ static int sort_items(SideBufs &A, SideBufs &B, PrepBufs &P, const SortKey &K, R
     else
         hipLaunchKernelGGL((k_morton<RSI, VC, false>), dim3(grid), dim3(1024), 0, s, ma, mb, P.seg, K.mbits,
                            P.keys[0], P.vals[0], P.hist, A.boxrep, A.G, rows, P.flags);
-    return radix_sort<RSI>(P.keys, P.vals, P.hist, P.part, P.seg, K, s, kev);
+    if constexpr (VC) {
+        if (kc) return radix_sort<RSI, true>(P.keys, P.vals, P.hist, P.part, P.seg, K, s, kev);
+    }
+    return radix_sort<RSI, false>(P.keys, P.vals, P.hist, P.part, P.seg, K, s, kev);
 }
 
 void launch_prep(SideBufs &A, SideBufs &B, PrepBufs &P, const SortKey &K, RowState *rows,
