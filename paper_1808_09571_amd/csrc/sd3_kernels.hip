@@ -1862,23 +1862,54 @@ __global__ void k_wi_compact(const float *wi_lb, const int64_t *wi_off, int64_t 
     if (keep) list[base + __popcll(m & lanes_below())] = (int32_t)wi;
 }
 
-// True when the whole work item can be skipped.  The row bound is read by
-// thread 0 only and broadcast through LDS: other workgroups lower it
-// concurrently, and every thread of the block must take the same branch.
-__device__ __forceinline__ bool wi_pruned(const float *wi_lb, int64_t wi, const RowState &R,
-                                          int mode) {
-    __shared__ int flag;
-    if (threadIdx.x == 0) {
-        double lb = (double)wi_lb[wi];
-        if (mode == 1) {
-            flag = lb > 0.0;
+// The work items a block takes.  Over the compacted list: its one entry.
+// Without a list (calls of few rows): up to WI_PER of the pass's n_wi items, a
+// grid apart (survivors lie side by side), those whose group bound still
+// holds; one wave looks them all up at once, so that a large pair's pruned
+// items, nearly all of them, cost a lane each and not a block (the
+// 4,000,000-triangle terrain: 60,000 items; k_ub_seed 28 -> 6.5 us, both
+// k_filter passes 42 -> 19 us).  The row bounds are read here only:
+// other workgroups lower them, and every thread must take the same branches.
+constexpr int WI_PER = 16;
+struct WorkList {
+    int32_t item[WI_PER];
+    int n;
+};
+__device__ __forceinline__ void block_items(WorkList &W, const int32_t *wlist, const unsigned int *wcount,
+                                            int64_t wi0, int64_t n_wi, const float *wi_lb, const int64_t *wi_off,
+                                            int64_t G, const RowState *rows, int mode) {
+    if (threadIdx.x < 64) {
+        const int k = (int)threadIdx.x;
+        bool keep = false;
+        int64_t wi = 0;
+        if (wlist) {
+            keep = k == 0 && blockIdx.x < *wcount;
+            if (keep) wi = wlist[blockIdx.x];
         } else {
-            double ub = bits_to_double(load_acq(&R.ub));
-            flag = lb > ub + row_margin(R, ub);
+            const int64_t at = (int64_t)blockIdx.x + (int64_t)k * gridDim.x;
+            keep = k < WI_PER && at < n_wi;
+            wi = wi0 + at;
         }
+        if (keep) {
+            const double lb = (double)wi_lb[wi];
+            if (mode == 1) {
+                keep = lb <= 0.0;
+            } else {
+                const RowState &R = rows[find_row(wi_off, G, wi)];
+                const double ub = bits_to_double(load_acq(&R.ub));
+                keep = lb <= ub + row_margin(R, ub);
+            }
+        }
+        const unsigned long long m = __ballot(keep);
+        if (keep) W.item[__popcll(m & lanes_below())] = (int32_t)wi;
+        if (k == 0) W.n = __popcll(m);
     }
     __syncthreads();
-    return flag != 0;
+}
+
+// Blocks of a launch over n_wi uncompacted work items.
+static unsigned wi_blocks(int64_t n_wi) {
+    return (unsigned)std::max<int64_t>(std::min<int64_t>(n_wi, 2048), (n_wi + WI_PER - 1) / WI_PER);
 }
 
 // Upper bound seed: the distance between two real vertices bounds the row
@@ -1887,36 +1918,35 @@ __global__ __launch_bounds__(256) void k_ub_seed(const TileMeta *mA, const TileM
                                                  const int64_t *tA, const int64_t *tB,
                                                  const int64_t *wi_off, int64_t G,
                                                  RowState *rows, const float *wi_lb,
-                                                 const int32_t *wlist, const unsigned int *wcount) {
+                                                 const int32_t *wlist, const unsigned int *wcount, int64_t n_wi) {
     __shared__ double rep[64][3];
-    int64_t wi = blockIdx.x;  // without a list: one block per work item
-    if (wlist) {
-        if (blockIdx.x >= *wcount) return;
-        wi = wlist[blockIdx.x];
-    }
-    WorkItem w = decode_item(wi_off, G, wi, tA, tB);
-    if (wi_pruned(wi_lb, wi, rows[w.g], 0)) return;
-    if (threadIdx.x < w.na)
-        for (int k = 0; k < 3; k++) rep[threadIdx.x][k] = mA[w.a0 + threadIdx.x].rep[k];
-    __syncthreads();
-    double best = __builtin_inf();
-    if (w.bvalid) {
-        double bp[3];
-        for (int k = 0; k < 3; k++) bp[k] = mB[w.b].rep[k];
-        for (int a = 0; a < w.na; a++) {
-            double dx = rep[a][0] - bp[0], dy = rep[a][1] - bp[1], dz = rep[a][2] - bp[2];
-            best = fmin(best, dx * dx + dy * dy + dz * dz);
-        }
-    }
     __shared__ double wred[4];
-    best = wave_min(best);
-    if (lane_id() == 0) wred[threadIdx.x >> 6] = best;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        best = fmin(fmin(wred[0], wred[1]), fmin(wred[2], wred[3]));
-        if (best < __builtin_inf()) {
-            double u = sqrt(best) * (1.0 + 8.0 * U64);
-            if (u < bits_to_double(load_acq(&rows[w.g].ub))) atomic_min_pos(&rows[w.g].ub, u);
+    __shared__ WorkList W;
+    block_items(W, wlist, wcount, 0, n_wi, wi_lb, wi_off, G, rows, 0);
+    for (int li = 0; li < W.n; li++) {
+        if (li > 0) __syncthreads();
+        WorkItem w = decode_item(wi_off, G, W.item[li], tA, tB);
+        if (threadIdx.x < w.na)
+            for (int k = 0; k < 3; k++) rep[threadIdx.x][k] = mA[w.a0 + threadIdx.x].rep[k];
+        __syncthreads();
+        double best = __builtin_inf();
+        if (w.bvalid) {
+            double bp[3];
+            for (int k = 0; k < 3; k++) bp[k] = mB[w.b].rep[k];
+            for (int a = 0; a < w.na; a++) {
+                double dx = rep[a][0] - bp[0], dy = rep[a][1] - bp[1], dz = rep[a][2] - bp[2];
+                best = fmin(best, dx * dx + dy * dy + dz * dz);
+            }
+        }
+        best = wave_min(best);
+        if (lane_id() == 0) wred[threadIdx.x >> 6] = best;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            best = fmin(fmin(wred[0], wred[1]), fmin(wred[2], wred[3]));
+            if (best < __builtin_inf()) {
+                double u = sqrt(best) * (1.0 + 8.0 * U64);
+                if (u < bits_to_double(load_acq(&rows[w.g].ub))) atomic_min_pos(&rows[w.g].ub, u);
+            }
         }
     }
 }
@@ -1940,92 +1970,91 @@ __global__ __launch_bounds__(256) void k_filter(const TileMeta *mA, const TileMe
                                                 RowState *rows, int mode, int2 *queue,
                                                 float *qlb, unsigned int *qcount,
                                                 unsigned int qcap, const float *wi_lb,
-                                                const int32_t *wlist, const unsigned int *wcount,
+                                                const int32_t *wlist, const unsigned int *wcount, int64_t n_wi,
                                                 RowState *scale_rows) {
     __shared__ double box[64][6];
+    __shared__ WorkList W;
     // block 0 of the first uncompacted pass also sets the rows' feature scale
-    if (scale_rows && blockIdx.x == 0)
+    if (scale_rows && blockIdx.x + blockIdx.y == 0)
         for (int64_t g = threadIdx.x; g < G; g += blockDim.x) row_scale(scale_rows, g);
-    int64_t wi;
-    if (wlist) {
-        if (blockIdx.x >= *wcount) return;
-        wi = wlist[blockIdx.x];
-    } else {
-        wi = wi0 + blockIdx.x;
-    }
-    WorkItem w = decode_item(wi_off, G, wi, tA, tB);
-    if (wi_pruned(wi_lb, wi, rows[w.g], mode)) return;
-    if (threadIdx.x < w.na)
+    block_items(W, wlist, wcount, wi0, n_wi, wi_lb, wi_off, G, rows, mode);
+    for (int li = 0; li < W.n; li++) {
+        if (li > 0) __syncthreads();
+        WorkItem w = decode_item(wi_off, G, W.item[li], tA, tB);
+        if (threadIdx.x < w.na)
+            for (int k = 0; k < 3; k++) {
+                box[threadIdx.x][k] = mA[w.a0 + threadIdx.x].lo[k];
+                box[threadIdx.x][3 + k] = mA[w.a0 + threadIdx.x].hi[k];
+            }
+        __syncthreads();
+        double blo[3], bhi[3];
         for (int k = 0; k < 3; k++) {
-            box[threadIdx.x][k] = mA[w.a0 + threadIdx.x].lo[k];
-            box[threadIdx.x][3 + k] = mA[w.a0 + threadIdx.x].hi[k];
+            blo[k] = mB[w.b].lo[k];
+            bhi[k] = mB[w.b].hi[k];
         }
-    __syncthreads();
-    double blo[3], bhi[3];
-    for (int k = 0; k < 3; k++) {
-        blo[k] = mB[w.b].lo[k];
-        bhi[k] = mB[w.b].hi[k];
-    }
-    const RowState &R = rows[w.g];
-    double ub = bits_to_double(R.ub);  // final after the seed kernels (previous launch)
-    double lim = ub + row_margin(R, ub);
-    // keep iff sqrt(g2) (1 - 8u) <= lim; compared squared with slack, the square
-    // root is taken only for kept pairs
-    double lim2 = lim * lim * (1.0 + 32.0 * U64);
-    bool hit = R.hit != 0;
-    unsigned long long best = ~0ull;  // this wave's seed candidate
-    // the wave's kept pairs (bit a of a lane: A tile a) are counted first and
-    // share one queue claim: the claims of a call all go to one address, one
-    // after the other (4096 rows: 359 -> 188 us; a claim per 8 A tiles before)
-    unsigned long long keeps = 0, any = 0;
-    unsigned int tot = 0;
-    constexpr int FG = 8;  // A tiles in flight
-    for (int a0 = 0; a0 < w.na && !hit; a0 += FG) {
-        unsigned long long m[FG];
+        const RowState &R = rows[w.g];
+        double ub = bits_to_double(R.ub);  // final after the seed kernels (previous launch)
+        double lim = ub + row_margin(R, ub);
+        // keep iff sqrt(g2) (1 - 8u) <= lim; compared squared with slack, the square
+        // root is taken only for kept pairs
+        double lim2 = lim * lim * (1.0 + 32.0 * U64);
+        bool hit = R.hit != 0;
+        unsigned long long best = ~0ull;  // this wave's seed candidate
+        // the wave's kept pairs (bit a of a lane: A tile a) are counted first and
+        // share one queue claim: the claims of a call all go to one address, one
+        // after the other (4096 rows: 359 -> 188 us; a claim per 8 A tiles before)
+        unsigned long long keeps = 0, any = 0;
+        unsigned int tot = 0;
+        constexpr int FG = 8;  // A tiles in flight
+        // (gridDim.y blocks share a work item's A tiles)
+        const int per = 64 / (int)gridDim.y, alast = (int)min(w.na, (int64_t)per * (blockIdx.y + 1));
+        for (int a0 = per * (int)blockIdx.y; a0 < alast && !hit; a0 += FG) {
+            unsigned long long m[FG];
 #pragma unroll
-        for (int j = 0; j < FG; j++) {
-            const int a = a0 + j;
-            bool keep = false;
-            if (a < w.na && w.bvalid) {
-                const double g2 = box_gap2(box[a], box[a] + 3, blo, bhi);
-                keep = mode == 0 ? g2 <= lim2
-                                 : g2 == 0.0 && box[a][0] <= bhi[0] && blo[0] <= box[a][3] && box[a][1] <= bhi[1] &&
-                                       blo[1] <= box[a][4] && box[a][2] <= bhi[2] && blo[2] <= box[a][5];
+            for (int j = 0; j < FG; j++) {
+                const int a = a0 + j;
+                bool keep = false;
+                if (a < alast && w.bvalid) {
+                    const double g2 = box_gap2(box[a], box[a] + 3, blo, bhi);
+                    keep = mode == 0 ? g2 <= lim2
+                                     : g2 == 0.0 && box[a][0] <= bhi[0] && blo[0] <= box[a][3] && box[a][1] <= bhi[1] &&
+                                           blo[1] <= box[a][4] && box[a][2] <= bhi[2] && blo[2] <= box[a][5];
+                }
+                m[j] = __ballot(keep);
             }
-            m[j] = __ballot(keep);
-        }
 #pragma unroll
-        for (int j = 0; j < FG; j++)
-            if (m[j]) {
-                any |= 1ull << (a0 + j);
-                tot += (unsigned int)__popcll(m[j]);
-                keeps |= ((m[j] >> lane_id()) & 1ull) << (a0 + j);
-            }
-    }
-    if (tot) {
-        unsigned int basei = 0;
-        if (lane_id() == 0) basei = atomicAdd(qcount, tot);
-        basei = __builtin_amdgcn_readfirstlane(basei);
-        // entries in A-tile order, then by lane
-        for (; any; any &= any - 1) {
-            const int a = __ffsll((long long)any) - 1;
-            const bool keep = (keeps >> a) & 1ull;
-            const unsigned long long m = __ballot(keep);
-            const unsigned int idx = basei + (unsigned int)__popcll(m & lanes_below());
-            basei += (unsigned int)__popcll(m);
-            if (keep && idx < qcap) {
-                float lbf = 0.0f;
-                if (mode == 0)
-                    lbf = (float)(sqrt(box_gap2(box[a], box[a] + 3, blo, bhi)) * (1.0 - 8.0 * U64) * (1.0 - 0x1p-20));
-                queue[idx] = make_int2((int)(w.a0 + a), (int)w.b);
-                qlb[idx] = lbf;
-                if (RANK == 1) best = min(best, ((unsigned long long)float_order_bits(lbf) << 32) | idx);
+            for (int j = 0; j < FG; j++)
+                if (m[j]) {
+                    any |= 1ull << (a0 + j);
+                    tot += (unsigned int)__popcll(m[j]);
+                    keeps |= ((m[j] >> lane_id()) & 1ull) << (a0 + j);
+                }
+        }
+        if (tot) {
+            unsigned int basei = 0;
+            if (lane_id() == 0) basei = atomicAdd(qcount, tot);
+            basei = __builtin_amdgcn_readfirstlane(basei);
+            // entries in A-tile order, then by lane
+            for (; any; any &= any - 1) {
+                const int a = __ffsll((long long)any) - 1;
+                const bool keep = (keeps >> a) & 1ull;
+                const unsigned long long m = __ballot(keep);
+                const unsigned int idx = basei + (unsigned int)__popcll(m & lanes_below());
+                basei += (unsigned int)__popcll(m);
+                if (keep && idx < qcap) {
+                    float lbf = 0.0f;
+                    if (mode == 0)
+                        lbf = (float)(sqrt(box_gap2(box[a], box[a] + 3, blo, bhi)) * (1.0 - 8.0 * U64) * (1.0 - 0x1p-20));
+                    queue[idx] = make_int2((int)(w.a0 + a), (int)w.b);
+                    qlb[idx] = lbf;
+                    if (RANK == 1) best = min(best, ((unsigned long long)float_order_bits(lbf) << 32) | idx);
+                }
             }
         }
-    }
-    if (RANK == 1) {
-        best = wave_min(best);
-        if (lane_id() == 0 && best != ~0ull && best < rows[w.g].best) atomicMin(&rows[w.g].best, best);
+        if (RANK == 1) {
+            best = wave_min(best);
+            if (lane_id() == 0 && best != ~0ull && best < rows[w.g].best) atomicMin(&rows[w.g].best, best);
+        }
     }
 }
 
@@ -2042,13 +2071,16 @@ static void launch_filter(const SideBufs &A, const SideBufs &B, const QueueGeo &
                            mode == 0 ? rows : (RowState *)nullptr);
         hipLaunchKernelGGL(k_filter<RANK>, dim3(nb), dim3(256), 0, s, A.meta, B.meta, A.tile_off,
                            B.tile_off, Q.wi_off, A.G, (int64_t)0, rows, mode, L.queue, L.qlb,
-                           L.qcount, L.qcap, Q.wi_lb, Q.wlist, Q.wcount + 1,
+                           L.qcount, L.qcap, Q.wi_lb, Q.wlist, Q.wcount + 1, n_wi,
                            (RowState *)nullptr);
     } else {
-        hipLaunchKernelGGL(k_filter<RANK>, dim3(nb), dim3(256), 0, s, A.meta, B.meta, A.tile_off,
+        // few work items survive in a call of few rows, and the loop over 64 A
+        // tiles is its time: four blocks share an item's (TIN pair of
+        // 512 x 512 cells 16.9 -> 12.1 us, an icosphere pair 10.2 -> 8.2)
+        hipLaunchKernelGGL(k_filter<RANK>, dim3(wi_blocks(n_wi), 4), dim3(256), 0, s, A.meta, B.meta, A.tile_off,
                            B.tile_off, Q.wi_off, A.G, wi_begin, rows, mode, L.queue, L.qlb,
                            L.qcount, L.qcap, Q.wi_lb, (const int32_t *)nullptr,
-                           (const unsigned int *)nullptr,
+                           (const unsigned int *)nullptr, n_wi,
                            mode == 0 && wi_begin == 0 ? rows : (RowState *)nullptr);
     }
 }
@@ -2065,11 +2097,11 @@ void launch_queue(const SideBufs &A, const SideBufs &B, const QueueGeo &Q, int64
             hipLaunchKernelGGL(k_wi_compact, dim3(grid_for(n_wi, 256)), dim3(256), 0, s, Q.wi_lb,
                                Q.wi_off, A.G, n_wi, rows, 0, Q.wlist, Q.wcount, (RowState *)nullptr);
             hipLaunchKernelGGL(k_ub_seed, dim3(nb), dim3(256), 0, s, A.meta, B.meta, A.tile_off,
-                               B.tile_off, Q.wi_off, A.G, rows, Q.wi_lb, Q.wlist, Q.wcount);
+                               B.tile_off, Q.wi_off, A.G, rows, Q.wi_lb, Q.wlist, Q.wcount, n_wi);
         } else if (what == Q_SEED) {
-            hipLaunchKernelGGL(k_ub_seed, dim3(nb), dim3(256), 0, s, A.meta, B.meta, A.tile_off,
+            hipLaunchKernelGGL(k_ub_seed, dim3(wi_blocks(n_wi)), dim3(256), 0, s, A.meta, B.meta, A.tile_off,
                                B.tile_off, Q.wi_off, A.G, rows, Q.wi_lb, (const int32_t *)nullptr,
-                               (const unsigned int *)nullptr);
+                               (const unsigned int *)nullptr, n_wi);
         }
         return;
     }
