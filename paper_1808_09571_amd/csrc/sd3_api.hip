@@ -149,6 +149,7 @@ struct Plan {
     std::vector<int64_t> sbA, sbB;      // [G+1] sort blocks of each row (rsi items each)
     int rsi = RS_ITEMS;                 // items per sort block
     int64_t max_row = 0;                // most triangles in one row of either side
+    int64_t max_verts = 0;              // and most vertices
     int64_t potential = 0;              // sum of tilesA * tilesB
 };
 
@@ -507,12 +508,13 @@ void plan_call(sd3_ctx *ctx, Workspace &ws, const sd3_geoms *a, const sd3_geoms 
         P.rsi = n <= SMALL_SORT ? RS_ITEMS : 2 * RS_ITEMS;
         P.sbA.assign(G + 1, 0);
         P.sbB.assign(G + 1, 0);
-        P.max_row = 0;
+        P.max_row = P.max_verts = 0;
         for (int64_t g = 0; g < G; g++) {
             const int64_t na = a->t_off[g + 1] - a->t_off[g], nb = b->t_off[g + 1] - b->t_off[g];
             P.sbA[g + 1] = P.sbA[g] + (na + P.rsi - 1) / P.rsi;
             P.sbB[g + 1] = P.sbB[g] + (nb + P.rsi - 1) / P.rsi;
             P.max_row = std::max(P.max_row, std::max(na, nb));
+            P.max_verts = std::max(P.max_verts, std::max(a->v_off[g + 1] - a->v_off[g], b->v_off[g + 1] - b->v_off[g]));
         }
     }
     // all offsets in one pinned staging copy: [A v_off | A t_off | A tiles |
@@ -558,8 +560,10 @@ void plan_call(sd3_ctx *ctx, Workspace &ws, const sd3_geoms *a, const sd3_geoms 
         C.PB.kc = cull ? (int32_t *)ws.buf(ws.kc, sizeof(int32_t) * 2 * G) : nullptr;
         C.PB.cub = cull && mode == 0 ? (double *)ws.buf(ws.cub, sizeof(double) * G) : nullptr;
         C.PB.oc = cull ? (uint8_t *)ws.buf(ws.oc, (size_t)(C.A.nv + C.B.nv)) : nullptr;
+        C.PB.local = P.rsi == RS_ITEMS && P.max_row <= RS_ITEMS;
+        C.PB.local_box = C.PB.local && P.max_verts <= ROWBOX_ROW;
         C.PB.seg = SortSeg{ds + 9 * G1, ds + 10 * G1, C.A.t_off, C.B.t_off, G, C.A.nt, P.sbA[G], nb, P.rsi,
-                           G >= SORT_TABLE_MIN_ROWS ? (SBlock *)ws.buf(ws.sorttab, sizeof(SBlock) * (nb + 1))
+                           G >= SORT_TABLE_MIN_ROWS && !C.PB.local ? (SBlock *)ws.buf(ws.sorttab, sizeof(SBlock) * (nb + 1))
                                                     : nullptr,
                            C.PB.kc, cull ? (int32_t *)ws.buf(ws.bn, sizeof(int32_t) * (nb + 1)) : nullptr};
     }

@@ -79,6 +79,8 @@ struct SortSeg {
     int32_t *bn;                   // [nb] kept items per sort block of a culling call (the key
                                    // kernel writes them first in the block), else nullptr
 };
+// Vertices of a row that one block reduces to its box.
+constexpr int64_t ROWBOX_ROW = 8192;
 // Calls of at least this many rows build the sort-block table first.
 constexpr int64_t SORT_TABLE_MIN_ROWS = 64;
 
@@ -98,6 +100,8 @@ struct PrepBufs {
                         // bound of the row distance plus a margin), else nullptr
                         // (intersects culls by the box itself)
     SortSeg seg;
+    bool local;         // every row fits one sort block: keys and sort in one launch
+    bool local_box;     // and has at most ROWBOX_ROW vertices a side: a block per row box
     uint32_t *flags;    // [2] validation flags of A and B (the key kernel checks indices)
 };
 
