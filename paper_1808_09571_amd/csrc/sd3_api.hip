@@ -1135,12 +1135,14 @@ sd3_status sd3_segments(sd3_ctx *ctx, int32_t op, const double *seg, int64_t n, 
         }
         const int64_t ntiles = (nt + SEG_MESH_TILE - 1) / SEG_MESH_TILE;
         const SegTree T = seg_tree(nt);
-        // [nodes | triangles | mesh box]
-        char *mb = (char *)ensure(ws.seg_mesh, (size_t)SEG_NODE_BYTES * T.nodes +
-                                                   sizeof(double) * (SEG_MESH_FIELDS * nt + 6) + 64);
+        // [nodes | FP32 triangles | triangles | mesh box | order]
+        const size_t nb = (size_t)SEG_NODE_BYTES * T.nodes + (size_t)16 * SEG_TRI4 * nt;
+        char *mb = (char *)ensure(ws.seg_mesh, nb + sizeof(double) * (SEG_MESH_FIELDS * nt + 6) +
+                                                   sizeof(int32_t) * nt + 64);
         float *nodes = (float *)mb;
-        double *P = (double *)(mb + (size_t)SEG_NODE_BYTES * T.nodes);
+        double *P = (double *)(mb + nb);
         unsigned long long *box = (unsigned long long *)(P + SEG_MESH_FIELDS * nt);
+        int32_t *order = (int32_t *)(box + 6);
         unsigned int *sc = (unsigned int *)ensure(ws.scalars, SCALAR_BYTES);
         uint32_t *flags = (uint32_t *)sc;
         unsigned long long *cnt = (unsigned long long *)(sc + 16);
@@ -1154,10 +1156,10 @@ sd3_status sd3_segments(sd3_ctx *ctx, int32_t op, const double *seg, int64_t n, 
         // the contents of device inputs are checked by the first kernel; the
         // others clamp every index into the mesh and write no result while a
         // flag is set, so that the flags are read with the counters at the end
-        launch_seg_validate(dseg, n, xyz, nv, tri, nt, flags, cnt, box, s);
+        launch_seg_validate(dseg, n, xyz, nv, tri, nt, order, flags, cnt, box, s);
         ensure_pinned(ctx, 0);
         char *rb = readback_area(ctx);
-        launch_seg_mesh(xyz, nv, tri, nt, T, box, P, nodes, s);
+        launch_seg_mesh(xyz, nv, tri, nt, T, box, order, P, nodes, s);
         int &gp = ctx->seg_grid[mode][T.top];
         // four blocks for each that is resident: the waves' work differs, and
         // a finished one makes room for the next

@@ -296,14 +296,16 @@ void launch_volume(const double *xyz, const int32_t *tri, const int64_t *v_off, 
                    hipStream_t s);
 
 // Segments / points against one mesh (sd3_segments.hip).  Mesh preparation:
-// P [nt][S_NTRI] FP64 triangles and the nodes of a tree of bounding cylinders
-// (level 0: the triangles; a node has SEG_FAN children), relative to the
-// mesh's box (ordered bits).  flags[0] (segments) and flags[1] (mesh) take the
+// order (the triangles' places along a curve, in runs of RS_ITEMS), P
+// [nt][S_NTRI] FP64 triangles, and the nodes of a tree of bounding cylinders
+// (level 0: the triangles; a node has SEG_FAN children) followed by the FP32
+// triangles, relative to the mesh's box (ordered bits).  flags[0] (segments) and flags[1] (mesh) take the
 // validation bits; cnt[0..2]: triangle bounds, full pair tests, exact tests.
 constexpr int SEG_MESH_TILE = 64;   // triangles a preparation wave takes
 constexpr int SEG_MESH_FIELDS = 18; // S_NTRI
 constexpr int SEG_FAN = 8;
 constexpr int SEG_NODE_BYTES = 32;
+constexpr int SEG_TRI4 = 5;         // 16-byte words of a triangle in FP32 (corners, dual basis, 1 / |edge|^2)
 constexpr int SEG_LEVELS = 9;       // 16 * 8^7 = 2^25 triangles have levels 0..7
 struct SegTree {
     uint32_t off[SEG_LEVELS], cnt[SEG_LEVELS];  // first node and nodes of each level
@@ -312,10 +314,10 @@ struct SegTree {
 };
 SegTree seg_tree(int64_t nt);
 void launch_seg_validate(const double *seg, int64_t n, const double *xyz, int64_t nv, const int32_t *tri,
-                         int64_t nt, uint32_t *flags, unsigned long long *cnt, unsigned long long *box,
-                         hipStream_t s);
+                         int64_t nt, int32_t *order, uint32_t *flags, unsigned long long *cnt,
+                         unsigned long long *box, hipStream_t s);
 void launch_seg_mesh(const double *xyz, int64_t nv, const int32_t *tri, int64_t nt, const SegTree &T,
-                     const unsigned long long *box, double *P, float *nodes, hipStream_t s);
+                     const unsigned long long *box, const int32_t *order, double *P, float *nodes, hipStream_t s);
 int seg_blocks_per_cu(int mode, const SegTree &T);
 // mode 0: dist (+ hit if non-null), 1: hit = intersects, 2: hit = distance <= r
 void launch_segs(int mode, const double *seg, int64_t n, const double *P, int64_t nt, const SegTree &T,

@@ -12,36 +12,40 @@
 // the mesh path (a zero-area triangle is the union of its edges), so the
 // values are those sd3_distance returns for the same inputs.
 //
-// Layout: the mesh is prepared once per call into FP64 triangles (S_NTRI
-// fields) and a tree of bounding cylinders over groups of 8, 64, 512, ...
-// consecutive triangles in FP32 (SegNode, 32 bytes; level 0 bounds the single
-// triangles).  One wave owns 64 segments.  It tests the nodes of the top
-// level (at most 16) against all of them, and keeps the (segment, node) pairs
-// that survive on one LDS stack per level; from then on a lane works on any
-// segment's pair: 64 pairs of one level are popped together, each lane tests
-// its node's eight children, and the survivors are compacted with ballots
-// onto the level below, the deepest level with 64 pairs first, so that the
-// lanes stay full however the segments differ.  Triangle pairs that are still
-// live when popped are gathered 64 at a time for the FP64 test.
+// Layout: the mesh is prepared once per call, each run of RS_ITEMS triangles in
+// the order of a Hilbert curve, into FP64 triangles (S_NTRI fields), FP32
+// triangles (SEG_TRI4 words) and a tree of bounding cylinders over groups of
+// 8, 64, 512, ... consecutive triangles in FP32 (SegNode, 32 bytes; level 0
+// bounds the single triangles).  One wave owns 64 segments.  It tests the
+// nodes of the top level (at most 16) against all of them, and keeps the
+// (segment, node) pairs that survive on one LDS stack per level; from then on
+// a lane works on any segment's pair: 64 pairs of one level are popped
+// together, each lane tests its node's eight children, and the survivors are
+// compacted with ballots onto the level below, the deepest level with 64 pairs
+// first, so that the lanes stay full however the segments differ.  Distances
+// take the FP32 bounds of the triangle pairs still live when popped, and what
+// these leave is gathered for the FP64 test until the list is full or nothing
+// else is to do: the bounds are at their lowest by then.
 //
-// Measured (perf/cases.py's segment cases; before: every lane looped over the
-// boxes of whole 64-triangle tiles, one scalar load chain per triangle, and
-// crossing segments ran exact arithmetic): 5,000,000 segments against a
-// 500-face body, distance, 14.2 -> 3.06 ms (119 triangle bounds and 8.4 FP64
-// tests a segment; 335 and 12.9 before); 300,000 within 2 of a 20,480-face
-// body 2.44 -> 0.31 ms.  Bound by FP32 and FP64 vector instructions and, at
-// three waves a SIMD (registers of the FP64 test; 8 KB of LDS and 2.3 KB a
-// level), the latency of the node gathers.
+// Measured (before: every lane looped over the boxes of whole 64-triangle
+// tiles, one scalar load chain per triangle, and crossing segments ran exact
+// arithmetic): 5,000,000 segments against a 500-face body, distance, 14.1 ->
+// 2.04 ms (75 triangle bounds and 2.6 FP64 tests a segment; 335 and 12.9
+// before); 300,000 within 2 of a 20,480-face body 2.27 -> 0.19 ms.  Of that,
+// on the first case's pass: FP64 tests right after the cylinders, in the
+// input's order, 2.91 ms; FP32 bounds and the late FP64 tests 2.40; the first
+// vertices' Morton order -> the centroids' Hilbert order 2.08.  Bound by FP32
+// vector instructions.
 #include <algorithm>
 
 #include "sd3_kernels.h"
+#include "sd3_sort.h"
 #include "sd3_pair64.h"
 #include "sd3_exact.h"
 
 namespace sd3 {
 
 constexpr int FAN = SEG_FAN;      // children per node
-constexpr int SEEDS = 64;         // triangle centres a segment's first upper bound is taken over
 constexpr int STACK = 64 + 64 * FAN;  // a level below 64 pairs takes one expansion
 
 // A bounding cylinder: every point of the node's triangles is c + a n + y
@@ -73,28 +77,138 @@ __device__ __forceinline__ SegFrame seg_frame(const unsigned long long *box) {
     return f;
 }
 
+// Place of a cell (6 bits an axis) along a Hilbert curve (Skilling, 2004:
+// exchange and invert the low bits of the axes from the top bit down, then
+// Gray decode).
+__device__ __forceinline__ uint32_t hilbert18(uint32_t (&x)[3]) {
+#pragma unroll
+    for (uint32_t q = 32; q > 1; q >>= 1) {
+        const uint32_t m = q - 1;
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            const uint32_t t = (x[0] ^ x[i]) & m;
+            const bool b = (x[i] & q) != 0;
+            x[0] ^= b ? m : t;
+            x[i] ^= b ? 0u : t;
+        }
+    }
+    x[1] ^= x[0];
+    x[2] ^= x[1];
+    uint32_t t = 0;
+#pragma unroll
+    for (uint32_t q = 32; q > 1; q >>= 1) t ^= (x[2] & q) ? q - 1 : 0u;
+#pragma unroll
+    for (int i = 0; i < 3; i++) x[i] ^= t;
+    return spread10(x[2]) | (spread10(x[1]) << 1) | (spread10(x[0]) << 2);
+}
+
+// The order the tree takes the triangles in: each run of RS_ITEMS triangles by
+// the place of their centroids' cells of the run's own box on the curve, so
+// that a node's eight triangles are a patch and not a strip of the input's
+// order (results never depend on it).  Against Morton order, whose jumps make
+// long patches: 91 -> 75 triangle bounds a segment.  One block for run `run`; indices are clamped
+// into the mesh.
+__device__ __forceinline__ void order_run(int64_t run, const double *xyz, int64_t nv, const int32_t *tri, int64_t nt,
+                                          int32_t *order, LocalSort &L, double (&red)[16][6]) {
+    constexpr int PER = RS_ITEMS / 1024;
+    const int tid = (int)threadIdx.x;
+    const int64_t t0 = run * RS_ITEMS;
+    const int n = (int)min((int64_t)RS_ITEMS, nt - t0);
+    double p[PER][3], lo[3], hi[3];
+    for (int c = 0; c < 3; c++) {
+        lo[c] = __builtin_inf();
+        hi[c] = -__builtin_inf();
+    }
+#pragma unroll
+    for (int r = 0; r < PER; r++) {
+        const int64_t t = t0 + min(r * 1024 + tid, n - 1);
+        for (int c = 0; c < 3; c++) p[r][c] = 0.0;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            const int32_t v = tri[3 * t + k];
+            const int64_t vi = (v >= 0 && (int64_t)v < nv) ? v : 0;
+#pragma unroll
+            for (int c = 0; c < 3; c++) p[r][c] += xyz[3 * vi + c];
+        }
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            lo[c] = fmin(lo[c], p[r][c]);
+            hi[c] = fmax(hi[c], p[r][c]);
+        }
+    }
+    for (int c = 0; c < 3; c++) {
+        const double a = wave_min(lo[c]), b = wave_max(hi[c]);
+        if (lane_id() == 0) {
+            red[tid >> 6][c] = a;
+            red[tid >> 6][3 + c] = b;
+        }
+    }
+    __syncthreads();
+    double ext = 0.0;
+    for (int c = 0; c < 3; c++) {
+        double a = red[0][c], b = red[0][3 + c];
+        for (int w = 1; w < 16; w++) {
+            a = fmin(a, red[w][c]);
+            b = fmax(b, red[w][3 + c]);
+        }
+        lo[c] = a;
+        ext = fmax(ext, b - a);
+    }
+    const double sc = ext > 0.0 && ext < __builtin_inf() ? 64.0 / ext : 0.0;
+#pragma unroll
+    for (int r = 0; r < PER; r++) {
+        const int j = r * 1024 + tid;
+        uint32_t x[3];
+#pragma unroll
+        for (int c = 0; c < 3; c++) x[c] = (uint32_t)fmin(fmax((p[r][c] - lo[c]) * sc, 0.0), 63.0);
+        if (j < n) L.a[j] = (hilbert18(x) >> 2) << 16 | (uint32_t)j;
+    }
+    __syncthreads();
+    local_pass(L, L.a, L.b, n, 16);
+    local_pass(L, L.b, L.a, n, 24);
+    for (int j = tid; j < n; j += 1024) order[t0 + j] = (int32_t)(t0 + (int64_t)(L.a[j] & 0xffffu));
+}
+
+__device__ __forceinline__ uint32_t coord_flags(double v) {
+    const double x = fabs(v);
+    const uint32_t range = x != 0.0 && (x < 0x1p-256 || x > 0x1p256) ? V_RANGE : 0u;
+    return x <= 1.7976931348623157e308 ? range : (uint32_t)V_NONFINITE;
+}
+
 // Validation of the segment coordinates (flags[0]) and of the mesh
 // (coordinates and indices, flags[1]), and the mesh's box (ordered bits) from
-// its vertices; k_seg_clear set every word.
-__global__ __launch_bounds__(256) void k_seg_validate(const double *seg, int64_t n, const double *xyz,
-                                                      int64_t nv, const int32_t *tri, int64_t nt,
-                                                      uint32_t *flags, unsigned long long *box) {
-    __shared__ unsigned long long red[4][6];
-    uint32_t fs = 0, fm = 0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t first = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    for (int64_t i = first; i < 6 * n; i += stride) {
-        const double x = fabs(seg[i]);
-        if (!(x <= 1.7976931348623157e308)) fs |= V_NONFINITE;
-        else if (x != 0.0 && (x < 0x1p-256 || x > 0x1p256)) fs |= V_RANGE;
+// its vertices; k_seg_clear set every word.  The first blocks, one per run, put
+// the mesh's triangles in order meanwhile: the sort of a small mesh is a chain
+// of waits in one block that no other work needs yet.
+__global__ __launch_bounds__(1024) void k_seg_validate(const double *seg, int64_t n, const double *xyz,
+                                                       int64_t nv, const int32_t *tri, int64_t nt, int32_t *order,
+                                                       uint32_t *flags, unsigned long long *box) {
+    __shared__ LocalSort L;
+    __shared__ double red[16][6];
+    const int64_t runs = (nt + RS_ITEMS - 1) / RS_ITEMS;
+    if ((int64_t)blockIdx.x < runs) {
+        order_run(blockIdx.x, xyz, nv, tri, nt, order, L, red);
+        return;
     }
+    const int64_t block = (int64_t)blockIdx.x - runs;
+    uint32_t fs = 0, fm = 0;
+    const int64_t stride = ((int64_t)gridDim.x - runs) * blockDim.x;
+    const int64_t first = block * (int64_t)blockDim.x + threadIdx.x;
+    int64_t i0 = first;
+    for (; i0 + 7 * stride < 6 * n; i0 += 8 * stride) {  // (eight loads in flight)
+        double x[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) x[k] = seg[i0 + k * stride];
+#pragma unroll
+        for (int k = 0; k < 8; k++) fs |= coord_flags(x[k]);
+    }
+    for (; i0 < 6 * n; i0 += stride) fs |= coord_flags(seg[i0]);
     double lo[3] = {__builtin_inf(), __builtin_inf(), __builtin_inf()};
     double hi[3] = {-__builtin_inf(), -__builtin_inf(), -__builtin_inf()};
     for (int64_t i = first; i < nv; i += stride)
         for (int c = 0; c < 3; c++) {
-            const double v = xyz[3 * i + c], x = fabs(v);
-            if (!(x <= 1.7976931348623157e308)) fm |= V_NONFINITE;
-            else if (x != 0.0 && (x < 0x1p-256 || x > 0x1p256)) fm |= V_RANGE;
+            const double v = xyz[3 * i + c];
+            fm |= coord_flags(v);
             lo[c] = fmin(lo[c], v);
             hi[c] = fmax(hi[c], v);
         }
@@ -104,21 +218,21 @@ __global__ __launch_bounds__(256) void k_seg_validate(const double *seg, int64_t
     }
     if (fs) atomicOr(&flags[0], fs);
     if (fm) atomicOr(&flags[1], fm);
-    if ((int64_t)blockIdx.x * blockDim.x >= nv) return;  // (block-uniform)
+    if (block * (int64_t)blockDim.x >= nv) return;  // (block-uniform)
     for (int c = 0; c < 3; c++) {
         const double a = wave_min(lo[c]), b = wave_max(hi[c]);
         if (lane_id() == 0) {
-            red[threadIdx.x >> 6][c] = ordered_bits(a);
-            red[threadIdx.x >> 6][3 + c] = ordered_bits(b);
+            red[threadIdx.x >> 6][c] = a;
+            red[threadIdx.x >> 6][3 + c] = b;
         }
     }
     __syncthreads();
     if (threadIdx.x < 6) {
         const int c = threadIdx.x;
-        unsigned long long v = red[0][c];
-        for (int w = 1; w < 4; w++) v = c < 3 ? min(v, red[w][c]) : max(v, red[w][c]);
-        if (c < 3) atomicMin(&box[c], v);
-        else atomicMax(&box[c], v);
+        double v = red[0][c];
+        for (int w = 1; w < 16; w++) v = c < 3 ? fmin(v, red[w][c]) : fmax(v, red[w][c]);
+        if (c < 3) atomicMin(&box[c], ordered_bits(v));
+        else atomicMax(&box[c], ordered_bits(v));
     }
 }
 
@@ -178,20 +292,21 @@ __device__ __forceinline__ void group_node(const double (&x)[9], const double (&
     w += 0x1p-20 * w;
 }
 
-// Prepared mesh: triangle t's S_NTRI fields and the cylinders of levels 0, 1
-// and 2 (one wave per 64 triangles; indices are clamped into the mesh so that
-// invalid contents never address other memory).
+// Prepared mesh: the S_NTRI fields of the t-th triangle in the tree's order and
+// the cylinders of levels 0, 1 and 2 (one wave per 64 triangles; indices are
+// clamped into the mesh so that invalid contents never address other memory).
 __global__ __launch_bounds__(64) void k_seg_mesh(const double *xyz, int64_t nv, const int32_t *tri, int64_t nt,
-                                                 const unsigned long long *box, double *P, float4 *nodes,
-                                                 SegTree T) {
+                                                 const int32_t *order, const unsigned long long *box, double *P,
+                                                 float4 *nodes, SegTree T) {
     const SegFrame F = seg_frame(box);
     const int64_t t = blockIdx.x * (int64_t)64 + threadIdx.x;
     const bool in = t < nt;
     double x[9], a[3];
     double f[F_NTRI64];
     TriRef<double> R{f, 1};
+    const int64_t ti = order[in ? t : nt - 1];
     for (int k = 0; k < 3; k++) {
-        const int32_t v = tri[3 * (in ? t : nt - 1) + k];
+        const int32_t v = tri[3 * ti + k];
         const int64_t vi = (v >= 0 && (int64_t)v < nv) ? v : 0;
         for (int c = 0; c < 3; c++) {
             f[F_V + 3 * k + c] = xyz[3 * vi + c];
@@ -205,6 +320,15 @@ __global__ __launch_bounds__(64) void k_seg_mesh(const double *xyz, int64_t nv, 
         for (int k = 0; k < 3; k++) q[S_IE + k] = f[F_IE + k];
         for (int k = 0; k < 3; k++) q[S_G1 + k] = f[F_G1 + k];
         for (int k = 0; k < 3; k++) q[S_G2 + k] = f[F_G2 + k];
+        // in the frame (a scale by a power of two)
+        const double g = 1.0 / F.s;
+        float4 *o = nodes + 2 * (int64_t)T.nodes + SEG_TRI4 * t;
+        o[0] = make_float4((float)x[0], (float)x[1], (float)x[2], (float)x[3]);
+        o[1] = make_float4((float)x[4], (float)x[5], (float)x[6], (float)x[7]);
+        o[2] = make_float4((float)x[8], (float)(f[F_G1] * g), (float)(f[F_G1 + 1] * g), (float)(f[F_G1 + 2] * g));
+        o[3] = make_float4((float)(f[F_G2] * g), (float)(f[F_G2 + 1] * g), (float)(f[F_G2 + 2] * g),
+                           (float)(f[F_IE] * g * g));
+        o[4] = make_float4((float)(f[F_IE + 1] * g * g), (float)(f[F_IE + 2] * g * g), 0.0f, 0.0f);
     }
     for (int k = 0; k < 3; k++) {
         const int i = (k + 1) % 3, j = (k + 2) % 3;
@@ -357,6 +481,94 @@ __device__ __forceinline__ float node_bound2(const SegF &s, const float4 &a, con
     return B - slack;
 }
 
+// Bounds of the distance between a segment and a triangle of the frame in
+// FP32, as pair32 takes them for two triangles: each candidate is the vector
+// between a point of one and a point of the other up to rounding, the shortest
+// bounds the distance from above, and the separation along it from below.
+// With M the largest coordinate of the segment's ends and e = 2^-24, rounding
+// into the frame moves the points by at most e sqrt(3) (3 M + 1), the vector
+// and the separation (differences, three products, the quotient) add at most
+// 40 e (3 M + 1) in all; 128 e (M + 1) is allowed.  NaN (a segment beyond
+// FP32's range of the mesh) bounds nothing.
+struct SegBound {
+    float ub, lb;
+};
+__device__ __forceinline__ SegBound seg_tri32(const SegF &s, const float4 *T) {
+    const float4 a0 = T[0], a1 = T[1], a2 = T[2], a3 = T[3], a4 = T[4];
+    const float v[9] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w, a2.x};
+    const float g1[3] = {a2.y, a2.z, a2.w}, g2[3] = {a3.x, a3.y, a3.z}, ie[3] = {a3.w, a4.x, a4.y};
+    float uu = 0.0f, M = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        uu = fmaf(s.u[k], s.u[k], uu);
+        M = fmaxf(M, fmaxf(fabsf(s.p[k]), fabsf(s.p[k] + s.u[k])));
+    }
+    float best = __builtin_inff(), b[3] = {0.0f, 0.0f, 0.0f};
+    float e0[3], e2[3];
+#pragma unroll
+    for (int l = 0; l < 3; l++) {
+        float e[3], r[3], ee = 0.0f, bb = 0.0f, d = 0.0f, f = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            e[k] = v[3 * ((l + 1) % 3) + k] - v[3 * l + k];
+            r[k] = s.p[k] - v[3 * l + k];
+            if (l == 0) e0[k] = e[k];
+            if (l == 2) e2[k] = e[k];
+            ee = fmaf(e[k], e[k], ee);
+            bb = fmaf(e[k], s.u[k], bb);
+            d = fmaf(r[k], s.u[k], d);
+            f = fmaf(r[k], e[k], f);
+        }
+        const float D = fmaf(uu, ee, -(bb * bb));
+        float x = D > 0.0f ? fminf(fmaxf((bb * f - ee * d) * __builtin_amdgcn_rcpf(D), 0.0f), 1.0f) : 0.0f;
+        const float y = fminf(fmaxf(fmaf(bb, x, f) * ie[l], 0.0f), 1.0f);
+        x = fminf(fmaxf(fmaf(bb, y, -d) * s.iu, 0.0f), 1.0f);
+        float w[3], q = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            w[k] = fmaf(x, s.u[k], fmaf(-y, e[k], r[k]));
+            q = fmaf(w[k], w[k], q);
+        }
+        const bool better = q < best;
+        best = better ? q : best;
+#pragma unroll
+        for (int k = 0; k < 3; k++) b[k] = better ? w[k] : b[k];
+    }
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        float w[3], b1 = 0.0f, b2 = 0.0f, q = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            w[k] = (i ? s.p[k] + s.u[k] : s.p[k]) - v[k];
+            b1 = fmaf(g1[k], w[k], b1);
+            b2 = fmaf(g2[k], w[k], b2);
+        }
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+            w[k] = fmaf(b2, e2[k], fmaf(-b1, e0[k], w[k]));
+            q = fmaf(w[k], w[k], q);
+        }
+        const bool better = b1 >= 0.0f && b2 >= 0.0f && b1 + b2 <= 1.0f && q < best;
+        best = better ? q : best;
+#pragma unroll
+        for (int k = 0; k < 3; k++) b[k] = better ? w[k] : b[k];
+    }
+    float sep = __builtin_inff(), wu = 0.0f;
+#pragma unroll
+    for (int l = 0; l < 3; l++) {
+        float h = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 3; k++) h = fmaf(b[k], s.p[k] - v[3 * l + k], h);
+        sep = fminf(sep, h);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; k++) wu = fmaf(b[k], s.u[k], wu);
+    sep += fminf(wu, 0.0f);
+    const float err = 0x1p-17f * (M + 1.0f);
+    return {sqrtf(best) * (1.0f + 0x1p-20f) + err,
+            best > 0x1p-100f ? fmaf(sep, __builtin_amdgcn_rsqf(best), -err) : -__builtin_inff()};
+}
+
 // Squared FP32 threshold of an upper bound (frame units, rounded up).
 __device__ __forceinline__ float cull2(float ub) {
     const float T = ub * (1.0f + 0x1p-20f);
@@ -383,7 +595,9 @@ __global__ __launch_bounds__(64, 3) void k_segs(const double *seg, int64_t n, co
     __shared__ uint32_t done[64];            // hit (MODE 0, 1) or within (MODE 2)
     __shared__ uint32_t tstk[STACK];         // live (triangle, segment) pairs and their bounds
     __shared__ float tlb[STACK];
-    __shared__ uint32_t rdy[128];            // pairs to test
+    constexpr int RDY = MODE == 0 ? 192 : 128;
+    __shared__ uint32_t rdy[RDY];            // pairs to test, and MODE 0's bounds
+    __shared__ float rlb[MODE == 0 ? RDY : 1];
     extern __shared__ uint32_t nstk[];       // (node, segment) pairs, STACK per level 1..top
     if (flags[0] | flags[1]) return;  // invalid contents: outputs stay untouched
     const int lane = lane_id();
@@ -439,40 +653,72 @@ __global__ __launch_bounds__(64, 3) void k_segs(const double *seg, int64_t n, co
         sf[1][lane] = make_float4(me.u[1], me.u[2], me.iu, 0.0f);
         best[lane] = double_to_bits(__builtin_inf());
         done[lane] = mine ? 0u : 1u;
-        float ub = __builtin_inff();
-        if (MODE == 0 && nt > 0) {
-            // a first upper bound: the nearest of up to SEEDS triangle
-            // centres (wave-uniform loads), so that the cull is tight from
-            // the first node on; the returned value comes from the FP64
-            // tests alone
-            const int ns = (int)min((int64_t)SEEDS, nt);
-            float m = __builtin_inff();
-#pragma unroll 8
-            for (int k = 0; k < ns; k++) {
-                float r0[3], r1[3];
-                m = fminf(m, seg_point2(me, nodes[2 * (T.off[0] + (k * nt) / ns)], r0, r1));
-            }
-            // (q0 + q1 + 2 <= 2 (|p|^2 + |p + u|^2) + 14 for every centre)
-            float a = 0.0f;
-            for (int c = 0; c < 3; c++) {
-                const float e = me.p[c] + me.u[c];
-                a = fmaf(me.p[c], me.p[c], fmaf(e, e, a));
-            }
-            m = sqrtf(fmaf(CULL_EPS, 2.0f * a + 14.0f, m)) * (1.0f + 0x1p-22f);
-            if (m >= 0.0f) ub = m;
-        }
-        ubf[lane] = __float_as_uint(ub);
+        ubf[lane] = __float_as_uint(__builtin_inff());
         lds_sync();
+        const float4 *tri32 = nodes + 2 * (int64_t)T.nodes;
         int cl = 0;  // lane l holds the pairs on level l's stack
         unsigned rc = 0;
         const int ntop = nt > 0 ? (int)T.cnt[T.top] : 0;
         int tt = 0;
+        if (MODE == 0 && nt > 0) {
+            // a first upper bound: that of the triangle that a way down the
+            // tree by the nearest centre ends at (any one would do), so that
+            // few nodes meet it
+            uint32_t at = 0;
+            float m = __builtin_inff();
+            for (int t = 0; t < ntop; t++) {
+                float r0[3], r1[3];
+                const float d2 = seg_point2(me, nodes[2 * ((int64_t)T.off[T.top] + t)], r0, r1);
+                at = d2 < m ? (uint32_t)t : at;
+                m = fminf(m, d2);
+            }
+            for (int lv = T.top - 1; lv >= 0; lv--) {
+                const float4 *cn = nodes + 2 * (int64_t)T.off[lv];
+                const uint32_t ch = at * FAN, nch = T.cnt[lv];
+                float4 na[FAN];
+#pragma unroll
+                for (int c = 0; c < FAN; c++) na[c] = cn[2 * (int64_t)min(ch + (uint32_t)c, nch - 1)];
+                at = ch;
+                m = __builtin_inff();
+#pragma unroll
+                for (int c = 0; c < FAN; c++) {
+                    float r0[3], r1[3];
+                    const float d2 = seg_point2(me, na[c], r0, r1);
+                    at = d2 < m ? ch + (uint32_t)c : at;  // (past the end: the last child's equal)
+                    m = fminf(m, d2);
+                }
+            }
+            const SegBound sb = seg_tri32(me, tri32 + SEG_TRI4 * (int64_t)at);
+            if (sb.ub >= 0.0f) ubf[lane] = __float_as_uint(sb.ub);
+        }
         for (;;) {
             const unsigned long long full = __ballot(cl >= 64), any = __ballot(cl > 0);
-            if (rc >= 64 || (!any && tt == ntop)) {
-                // test the last (at most 64) pairs of the ready list
-                if (rc == 0) break;
+            const bool last = !any && tt == ntop;
+            if (rc > (unsigned)RDY - 64 || last) {
                 lds_sync();
+                if (MODE == 0) {
+                    // (bounds have come down since)
+                    unsigned m = 0;
+                    for (unsigned c = 0; c < rc; c += 64) {
+                        const unsigned j = min(c + (unsigned)lane, rc - 1);
+                        const uint32_t e = rdy[j];
+                        const float lb = rlb[j];
+                        const bool keep =
+                            c + (unsigned)lane < rc && !done[e & 63] && !(lb > __uint_as_float(ubf[e & 63]));
+                        const unsigned long long mk = __ballot(keep);
+                        lds_sync();
+                        if (keep) {
+                            rdy[m + __popcll(mk & below)] = e;
+                            rlb[m + __popcll(mk & below)] = lb;
+                        }
+                        m += (unsigned)__popcll(mk);
+                    }
+                    rc = m;
+                    lds_sync();
+                }
+                // test the last (at most 64) pairs of the ready list
+                if (rc == 0 && last) break;
+                if (rc < 64 && !last) continue;
                 const unsigned k = min(rc, 64u);
                 rc -= k;
                 const uint32_t e = (unsigned)lane < k ? rdy[rc + lane] : 0u;
@@ -538,9 +784,21 @@ __global__ __launch_bounds__(64, 3) void k_segs(const double *seg, int64_t n, co
                 const uint32_t e = lane < k ? tstk[c0 + lane] : 0u;
                 const int slot = (int)(e & 63);
                 const float t2 = MODE == 0 ? cull2(__uint_as_float(ubf[slot])) : MODE == 2 ? r2 : 0.0f;
-                const bool keep = lane < k && !done[slot] && !(tlb[c0 + (lane < k ? lane : 0)] > t2);
+                bool keep = lane < k && !done[slot] && !(tlb[c0 + (lane < k ? lane : 0)] > t2);
+                float lb = 0.0f;
+                if (MODE == 0 && keep) {
+                    const float4 s0 = sf[0][slot], s1 = sf[1][slot];
+                    const SegF sg{{s0.x, s0.y, s0.z}, {s0.w, s1.x, s1.y}, s1.z};
+                    const SegBound sb = seg_tri32(sg, tri32 + SEG_TRI4 * (int64_t)(e >> 6));
+                    lb = sb.lb;
+                    if (sb.ub >= 0.0f) atomicMin(&ubf[slot], __float_as_uint(sb.ub));
+                    keep = !(lb > fminf(sb.ub, __uint_as_float(ubf[slot])));
+                }
                 const unsigned long long mk = __ballot(keep);
-                if (keep) rdy[rc + __popcll(mk & below)] = e;
+                if (keep) {
+                    rdy[rc + __popcll(mk & below)] = e;
+                    if (MODE == 0) rlb[rc + __popcll(mk & below)] = lb;
+                }
                 rc += (unsigned)__popcll(mk);
                 continue;
             }
@@ -646,18 +904,19 @@ SegTree seg_tree(int64_t nt) {
 }
 
 void launch_seg_validate(const double *seg, int64_t n, const double *xyz, int64_t nv, const int32_t *tri,
-                         int64_t nt, uint32_t *flags, unsigned long long *cnt, unsigned long long *box,
-                         hipStream_t s) {
+                         int64_t nt, int32_t *order, uint32_t *flags, unsigned long long *cnt,
+                         unsigned long long *box, hipStream_t s) {
     hipLaunchKernelGGL(k_seg_clear, dim3(1), dim3(C_REPLICAS * C_NCOUNTERS), 0, s, flags, cnt, box);
     const int64_t work = std::max<int64_t>(6 * n, std::max<int64_t>(3 * nv, 3 * nt));
-    const unsigned grid = (unsigned)std::min<int64_t>(std::max<int64_t>((work + 255) / 256, 1), 4096);
-    hipLaunchKernelGGL(k_seg_validate, dim3(grid), dim3(256), 0, s, seg, n, xyz, nv, tri, nt, flags, box);
+    const int64_t runs = (nt + RS_ITEMS - 1) / RS_ITEMS;
+    const unsigned grid = (unsigned)(runs + std::min<int64_t>(std::max<int64_t>((work + 1023) / 1024, 1), 512));
+    hipLaunchKernelGGL(k_seg_validate, dim3(grid), dim3(1024), 0, s, seg, n, xyz, nv, tri, nt, order, flags, box);
 }
 
 void launch_seg_mesh(const double *xyz, int64_t nv, const int32_t *tri, int64_t nt, const SegTree &T,
-                     const unsigned long long *box, double *P, float *nodes, hipStream_t s) {
+                     const unsigned long long *box, const int32_t *order, double *P, float *nodes, hipStream_t s) {
     if (nt <= 0) return;
-    hipLaunchKernelGGL(k_seg_mesh, dim3((unsigned)((nt + 63) / 64)), dim3(64), 0, s, xyz, nv, tri, nt, box, P,
+    hipLaunchKernelGGL(k_seg_mesh, dim3((unsigned)((nt + 63) / 64)), dim3(64), 0, s, xyz, nv, tri, nt, order, box, P,
                        (float4 *)nodes, T);
     if (T.top >= 3) hipLaunchKernelGGL(k_seg_up, dim3(1), dim3(1024), 0, s, (float4 *)nodes, T);
 }

@@ -77,3 +77,22 @@ def test_flat_and_degenerate_meshes(ctx):
     k = np.arange(29, dtype=np.int32)
     _check(ctx, seg, (line, np.stack([k, k + 1, k + 1], axis=1)), 0.2)
     _check(ctx, seg, (np.array([[0.25, 0.5, -0.125]]), np.zeros((3, 3), np.int32)), 0.2)
+
+
+@pytest.mark.parametrize("nt,n", [(2047, 17), (2048, 64), (2049, 17), (4097, 17)])
+def test_runs_of_the_order(ctx, nt, n):
+    # the tree takes each 2048 triangles in the order of a curve: the edges of
+    # a run, triangles in no order at all
+    mesh = synth.random_triangle_soup(nt, nt, scale=1.0, size=0.05)
+    _check(ctx, _segments(nt, n, 1.0), mesh, 0.25)
+
+
+def test_every_triangle_as_near_as_any(ctx):
+    # points and short segments at the centre of a sphere, where no bound
+    # tells one triangle from another: the list of pairs to test runs full
+    x, t = synth.blob(2000, 1.0, (0.0, 0.0, 0.0), 3)
+    x = x / np.linalg.norm(x, axis=1, keepdims=True)
+    g = np.random.default_rng(5)
+    p = g.normal(size=(130, 3)) * np.array([0.0, 1e-9, 1e-6, 1e-3, 1e-2])[np.arange(130) % 5, None]
+    q = p + g.normal(size=(130, 3)) * np.array([0.0, 1e-7, 1e-3])[np.arange(130) % 3, None]
+    _check(ctx, np.stack([p, q], axis=1), (x, t), 0.99)
