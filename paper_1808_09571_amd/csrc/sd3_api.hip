@@ -295,9 +295,22 @@ sd3_status check_geoms(const sd3_geoms *g, std::string &msg) {
     return SD3_OK;
 }
 
+// No coordinate of n is refused.  Without branches, so that the compiler takes
+// several at once (60,000: 113 us as the loop that names the first one refused,
+// which runs only where there is one; 38 us).
+bool coords_ok(const double *v, int64_t n) {
+    unsigned bad = 0;
+    for (int64_t i = 0; i < n; i++) {
+        const double x = std::fabs(v[i]);
+        bad |= (unsigned)!(x <= 0x1p256) | ((unsigned)(x < 0x1p-256) & (unsigned)(x != 0.0));
+    }
+    return bad == 0;
+}
+
 sd3_status check_host_data(const sd3_geoms *g, std::string &msg) {
     int64_t nv = g->v_off[g->count];
-    for (int64_t i = 0; i < nv * 3; i++) {
+    const bool ok = coords_ok(g->xyz, 3 * nv);
+    for (int64_t i = 0; !ok && i < nv * 3; i++) {
         double x = std::fabs(g->xyz[i]);
         if (!(x <= 1.7976931348623157e308)) {
             msg = "non-finite coordinate at vertex " + std::to_string(i / 3);
@@ -1104,14 +1117,6 @@ sd3_status sd3_segments(sd3_ctx *ctx, int32_t op, const double *seg, int64_t n, 
     if (seg_mem == SD3_MEM_HOST) {
         st = check_host_data(mesh, msg);
         if (st != SD3_OK) return fail(ctx, st, msg);
-        for (int64_t i = 0; i < 6 * n; i++) {
-            const double x = std::fabs(seg[i]);
-            if (!(x <= 1.7976931348623157e308))
-                return fail(ctx, SD3_E_NONFINITE, "non-finite coordinate in segment " + std::to_string(i / 6));
-            if (x != 0.0 && (x < 0x1p-256 || x > 0x1p256))
-                return fail(ctx, SD3_E_RANGE, "coordinate magnitude outside [2^-256, 2^256] in segment " +
-                                                  std::to_string(i / 6));
-        }
     }
     hipStream_t s = (hipStream_t)stream;
     Workspace &ws = ctx->ws;
@@ -1166,6 +1171,19 @@ sd3_status sd3_segments(sd3_ctx *ctx, int32_t op, const double *seg, int64_t n, 
         if (gp == 0) gp = 4 * ctx->cus * seg_blocks_per_cu(mode, T);
         launch_segs(mode, dseg, n, P, nt, T, nodes, box, r, mode == 0 ? odist : nullptr, oflag, flags, cnt, gp, s);
         check(hipGetLastError(), "kernel launch");
+        // segments in host memory are checked here while the kernels run on
+        // them (which bear any contents, as above), before a result is copied
+        if (seg_mem == SD3_MEM_HOST && !coords_ok(seg, 6 * n)) {
+            check(hipStreamSynchronize(s), "sync");
+            for (int64_t i = 0; i < 6 * n; i++) {
+                const double x = std::fabs(seg[i]);
+                if (!(x <= 1.7976931348623157e308))
+                    return fail(ctx, SD3_E_NONFINITE, "non-finite coordinate in segment " + std::to_string(i / 6));
+                if (x != 0.0 && (x < 0x1p-256 || x > 0x1p256))
+                    return fail(ctx, SD3_E_RANGE, "coordinate magnitude outside [2^-256, 2^256] in segment " +
+                                                      std::to_string(i / 6));
+            }
+        }
         check(hipMemcpyAsync(rb, sc, SCALAR_BYTES, hipMemcpyDeviceToHost, s), "D2H counters");
         if (seg_mem == SD3_MEM_HOST && n > 0) {
             if (dist) check(hipMemcpyAsync(dist, odist, sizeof(double) * n, hipMemcpyDeviceToHost, s), "D2H dist");

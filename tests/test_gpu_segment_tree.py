@@ -96,3 +96,26 @@ def test_every_triangle_as_near_as_any(ctx):
     p = g.normal(size=(130, 3)) * np.array([0.0, 1e-9, 1e-6, 1e-3, 1e-2])[np.arange(130) % 5, None]
     q = p + g.normal(size=(130, 3)) * np.array([0.0, 1e-7, 1e-3])[np.arange(130) % 3, None]
     _check(ctx, np.stack([p, q], axis=1), (x, t), 0.99)
+
+
+@pytest.mark.parametrize("bad,name", [(np.nan, "SD3_E_NONFINITE"), (-np.inf, "SD3_E_NONFINITE"),
+                                      (np.nextafter(2.0 ** 256, np.inf), "SD3_E_RANGE"),
+                                      (np.nextafter(2.0 ** -256, 0.0), "SD3_E_RANGE"), (5e-324, "SD3_E_RANGE")])
+def test_refused_host_segments(ctx, bad, name):
+    # host segments are checked while the kernels run on them: the first one
+    # refused is named, no output is written, and the next call is unharmed
+    import ctypes
+    mb = sd3.Batch.from_packed(synth.pack([synth.blob(100, 1.0, (0.0, 0.0, 0.0), 2)]))
+    seg = _segments(4, 70, 1.0)
+    good = ctx.segments("distance", seg, mb)
+    wrong = seg.copy()
+    wrong[66, 1, 2] = wrong[69, 0, 0] = bad
+    d, f = np.full(70, 7.0), np.full(70, 7, np.uint8)
+    g = mb.geoms()
+    st = ctx.lib.sd3_segments(ctx.handle, sd3.SEG_OP["distance"], wrong.ctypes.data, 70, sd3.MEM_HOST,
+                              ctypes.byref(g), 0.0, d.ctypes.data, f.ctypes.data, None, None)
+    with pytest.raises(sd3.SD3Error, match="segment 66") as e:
+        ctx._raise(st)
+    assert e.value.name == name and (d == 7.0).all() and (f == 7).all()
+    again = ctx.segments("distance", seg, mb)
+    assert np.array_equal(good[0], again[0]) and np.array_equal(good[1], again[1])
