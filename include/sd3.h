@@ -280,7 +280,7 @@ sd3_status sd3_volume(sd3_ctx *ctx, const sd3_geoms *g, double *vol, sd3_stats *
  * Results equal those of sd3_distance / sd3_intersects on the segment as the
  * degenerate triangle (P0, P1, P1): FP64 distances, exact flags; an empty mesh
  * gives +inf and 0.  Errors as for sd3_distance (validation of the segment
- * coordinates and of the mesh); outputs untouched on error.  stats: box tests
+ * coordinates and of the mesh); outputs untouched on error.  stats: triangle bounds
  * in tri_pairs_boxed, FP64 pair tests in tri_pairs_fp64, exact tests in exact.
  */
 #define SD3_SEG_DISTANCE 0

@@ -106,8 +106,8 @@ __device__ __forceinline__ uint32_t hilbert18(uint32_t (&x)[3]) {
 // the place of their centroids' cells of the run's own box on the curve, so
 // that a node's eight triangles are a patch and not a strip of the input's
 // order (results never depend on it).  Against Morton order, whose jumps make
-// long patches: 91 -> 75 triangle bounds a segment.  One block for run `run`; indices are clamped
-// into the mesh.
+// long patches: 91 -> 75 triangle bounds a segment.  One block for run `run`;
+// indices are clamped into the mesh.
 __device__ __forceinline__ void order_run(int64_t run, const double *xyz, int64_t nv, const int32_t *tri, int64_t nt,
                                           int32_t *order, LocalSort &L, double (&red)[16][6]) {
     constexpr int PER = RS_ITEMS / 1024;
