@@ -31,11 +31,13 @@
 // tiles, one scalar load chain per triangle, and crossing segments ran exact
 // arithmetic): 5,000,000 segments against a 500-face body, distance, 14.1 ->
 // 2.04 ms (75 triangle bounds and 2.6 FP64 tests a segment; 335 and 12.9
-// before); 300,000 within 2 of a 20,480-face body 2.27 -> 0.19 ms.  Of that,
+// before); 300,000 within 2 of a 20,480-face body 2.27 -> 0.17 ms.  Of that,
 // on the first case's pass: FP64 tests right after the cylinders, in the
 // input's order, 2.91 ms; FP32 bounds and the late FP64 tests 2.40; the first
 // vertices' Morton order -> the centroids' Hilbert order 2.08.  Bound by FP32
-// vector instructions.
+// vector instructions.  The other operators' threshold never moves, so they keep
+// no bounds in LDS (8.2 -> 5.1 KB a wave and 2.3 KB a level: two more waves a CU
+// on the 20,480 faces, 189 -> 174 us).
 #include <algorithm>
 
 #include "sd3_kernels.h"
@@ -590,11 +592,11 @@ __global__ __launch_bounds__(64, 3) void k_segs(const double *seg, int64_t n, co
                                              double r, double *dist, uint8_t *hit, const uint32_t *flags,
                                              unsigned long long *cnt) {
     __shared__ float4 sf[2][64];             // in the frame: p and u.x, u.y u.z iu
-    __shared__ unsigned long long best[64];  // squared distance bits
-    __shared__ uint32_t ubf[64];             // upper bound in the frame, rounded up (bits)
+    __shared__ unsigned long long best[MODE == 0 ? 64 : 1];  // squared distance bits
+    __shared__ uint32_t ubf[MODE == 0 ? 64 : 1];  // upper bound in the frame, rounded up (bits)
     __shared__ uint32_t done[64];            // hit (MODE 0, 1) or within (MODE 2)
     __shared__ uint32_t tstk[STACK];         // live (triangle, segment) pairs and their bounds
-    __shared__ float tlb[STACK];
+    __shared__ float tlb[MODE == 0 ? STACK : 1];  // (the others' threshold stays, so these passed)
     constexpr int RDY = MODE == 0 ? 192 : 128;
     __shared__ uint32_t rdy[RDY];            // pairs to test, and MODE 0's bounds
     __shared__ float rlb[MODE == 0 ? RDY : 1];
@@ -651,9 +653,11 @@ __global__ __launch_bounds__(64, 3) void k_segs(const double *seg, int64_t n, co
         }
         sf[0][lane] = make_float4(me.p[0], me.p[1], me.p[2], me.u[0]);
         sf[1][lane] = make_float4(me.u[1], me.u[2], me.iu, 0.0f);
-        best[lane] = double_to_bits(__builtin_inf());
         done[lane] = mine ? 0u : 1u;
-        ubf[lane] = __float_as_uint(__builtin_inff());
+        if (MODE == 0) {
+            best[lane] = double_to_bits(__builtin_inf());
+            ubf[lane] = __float_as_uint(__builtin_inff());
+        }
         lds_sync();
         const float4 *tri32 = nodes + 2 * (int64_t)T.nodes;
         int cl = 0;  // lane l holds the pairs on level l's stack
@@ -783,8 +787,8 @@ __global__ __launch_bounds__(64, 3) void k_segs(const double *seg, int64_t n, co
             if (lv == 0) {
                 const uint32_t e = lane < k ? tstk[c0 + lane] : 0u;
                 const int slot = (int)(e & 63);
-                const float t2 = MODE == 0 ? cull2(__uint_as_float(ubf[slot])) : MODE == 2 ? r2 : 0.0f;
-                bool keep = lane < k && !done[slot] && !(tlb[c0 + (lane < k ? lane : 0)] > t2);
+                bool keep = lane < k && !done[slot];
+                if (MODE == 0) keep = keep && !(tlb[c0 + (lane < k ? lane : 0)] > cull2(__uint_as_float(ubf[slot])));
                 float lb = 0.0f;
                 if (MODE == 0 && keep) {
                     const float4 s0 = sf[0][slot], s1 = sf[1][slot];
@@ -848,7 +852,7 @@ __global__ __launch_bounds__(64, 3) void k_segs(const double *seg, int64_t n, co
                 if (lv == 1) {
                     if (keep) {
                         tstk[at] = en;
-                        tlb[at] = B[c];
+                        if (MODE == 0) tlb[at] = B[c];
                     }
                 } else if (keep) {
                     nstk[(lv - 2) * STACK + at] = en;
