@@ -358,47 +358,46 @@ __global__ __launch_bounds__(64) void k_seg_mesh(const double *xyz, int64_t nv, 
 }
 
 // Levels 3 and up, each from the level below (one block; a mesh of 2^25
-// triangles has 2^16 nodes in level 3).
+// triangles has 2^16 nodes in level 3).  A lane takes a child, eight lanes a
+// node: a level is one round of loads and a few reductions (a thread a node,
+// walking its children: 8.5 us for two levels, 4.7 now).
 __global__ __launch_bounds__(1024) void k_seg_up(float4 *nodes, SegTree T) {
+    auto dmin = [](double p, double q) { return fmin(p, q); };
+    auto dmax = [](double p, double q) { return fmax(p, q); };
+    auto dadd = [](double p, double q) { return p + q; };
     for (int l = 3; l <= T.top; l++) {
-        for (int64_t i = threadIdx.x; i < (int64_t)T.cnt[l]; i += blockDim.x) {
-            const int64_t k0 = i * FAN, k1 = min((int64_t)T.cnt[l - 1], k0 + FAN);
-            const float4 *ch = nodes + 2 * (int64_t)T.off[l - 1];
-            double lo[3], hi[3], s[3] = {0.0, 0.0, 0.0};
+        const float4 *ch = nodes + 2 * (int64_t)T.off[l - 1];
+        const int64_t n = T.cnt[l], nch = T.cnt[l - 1];
+        // (a whole group of eight lanes goes round, or none of it)
+        for (int64_t i = threadIdx.x / FAN; i < n; i += blockDim.x / FAN) {
+            const int64_t j = i * FAN + threadIdx.x % FAN;
+            const bool in = j < nch;
+            const float4 a = ch[2 * (in ? j : nch - 1)], b = ch[2 * (in ? j : nch - 1) + 1];
+            const double cc[3] = {a.x, a.y, a.z}, nn[3] = {b.x, b.y, b.z};
+            const double rad = (double)a.w + (double)b.w;
+            float c[3], m[3];
+            double s[3];
             for (int k = 0; k < 3; k++) {
-                lo[k] = __builtin_inf();
-                hi[k] = -__builtin_inf();
+                const double lo = lanes_reduce<FAN>(in ? cc[k] - rad : __builtin_inf(), dmin);
+                const double hi = lanes_reduce<FAN>(in ? cc[k] + rad : -__builtin_inf(), dmax);
+                s[k] = lanes_reduce<FAN>(in ? nn[k] * (double)a.w * (double)a.w : 0.0, dadd);
+                c[k] = (float)fmin(fmax(0.5 * lo + 0.5 * hi, -1.0), 1.0);
             }
-            for (int64_t j = k0; j < k1; j++) {
-                const float4 a = ch[2 * j], b = ch[2 * j + 1];
-                const double cc[3] = {a.x, a.y, a.z}, nn[3] = {b.x, b.y, b.z};
-                const double rad = (double)a.w + (double)b.w;
-                for (int k = 0; k < 3; k++) {
-                    lo[k] = fmin(lo[k], cc[k] - rad);
-                    hi[k] = fmax(hi[k], cc[k] + rad);
-                    s[k] += nn[k] * (double)a.w * (double)a.w;
-                }
-            }
-            float c[3], n[3];
-            for (int k = 0; k < 3; k++) c[k] = (float)fmin(fmax(0.5 * lo[k] + 0.5 * hi[k], -1.0), 1.0);
-            unit_dir(s, n);
-            double rho = 0.0, w = 0.0;
-            for (int64_t j = k0; j < k1; j++) {
-                // a child's point c_j + a n_j + y: along n and across it
-                const float4 a = ch[2 * j], b = ch[2 * j + 1];
-                const double d0 = (double)a.x - c[0], d1 = (double)a.y - c[1], d2 = (double)a.z - c[2];
-                const double h = n[0] * d0 + n[1] * d1 + n[2] * d2;
-                const double l0 = d0 - h * n[0], l1 = d1 - h * n[1], l2 = d2 - h * n[2];
-                const double co = fabs((double)n[0] * b.x + (double)n[1] * b.y + (double)n[2] * b.z);
-                const double si = sqrt(fmax(1.0 - co * co, 0.0) + 0x1p-18);
-                const double cw = fmin(co + 0x1p-18, 1.0 + 0x1p-18);
-                rho = fmax(rho, sqrt(l0 * l0 + l1 * l1 + l2 * l2) + (double)a.w + (double)b.w * si);
-                w = fmax(w, fabs(h) + (double)b.w * cw + (double)a.w * si);
-            }
+            unit_dir(s, m);
+            // the child's point c_j + a n_j + y: along m and across it
+            const double d0 = cc[0] - c[0], d1 = cc[1] - c[1], d2 = cc[2] - c[2];
+            const double h = m[0] * d0 + m[1] * d1 + m[2] * d2;
+            const double l0 = d0 - h * m[0], l1 = d1 - h * m[1], l2 = d2 - h * m[2];
+            const double co = fabs((double)m[0] * b.x + (double)m[1] * b.y + (double)m[2] * b.z);
+            const double si = sqrt(fmax(1.0 - co * co, 0.0) + 0x1p-18);
+            const double cw = fmin(co + 0x1p-18, 1.0 + 0x1p-18);
+            const double r = sqrt(l0 * l0 + l1 * l1 + l2 * l2) + (double)a.w + (double)b.w * si;
+            const double v = fabs(h) + (double)b.w * cw + (double)a.w * si;
+            double rho = lanes_reduce<FAN>(in ? r : 0.0, dmax), w = lanes_reduce<FAN>(in ? v : 0.0, dmax);
             // (no two points of the frame are farther apart than 2 sqrt(3))
             rho = fmin((rho + 0x1p-18 * w) * (1.0 + 0x1p-18), 3.4642);
             w = fmin(w * (1.0 + 0x1p-18), 3.4642);
-            write_node(nodes, T.off[l] + i, c, rho, n, w);
+            if (threadIdx.x % FAN == 0) write_node(nodes, T.off[l] + i, c, rho, m, w);
         }
         __threadfence_block();
         __syncthreads();
