@@ -2459,8 +2459,9 @@ __device__ __forceinline__ double fp32_upper(float dm, float eu) {
 __device__ __forceinline__ bool axis_far32(float sep, float uu, float elb, float limf) {
     return uu >= 0x1p-120f && sep * __builtin_amdgcn_rsqf(uu) - elb > limf;
 }
-// FP64: the rounding (2^-47 of the extent) is far below the margin in T2
-// (2^-36 of it).
+// FP64, on corners taken from one of them: the rounding (2^-47 of the extent)
+// is far below the margin in T2 (2^-36 of it).  That of absolute coordinates
+// is not, from some 2^15 extents off the origin on.
 __device__ __forceinline__ bool axis_far64(double sep, double uu, double T2) {
     return sep > 0.0 && sep * sep > T2 * uu * (1.0 + 16.0 * U64);
 }
@@ -2860,16 +2861,25 @@ __global__ __launch_bounds__(64, PREC == 0 && TK <= 64 ? 3 : 1) void k_pairs(con
                 const bool on = (unsigned)lane < n;
                 const uint32_t pr = on ? ring[(rd + lane) & (RING - 1)] : 0u;
                 const Tt *pa = sA + (pr & 255) * VS, *pb = sB + (pr >> 8) * VS;
-                Tt u[3], uu = 0, amax = 0, bmin = 0;
+                // FP32 corners are offsets in A's frame; FP64 ones are absolute
+                // and taken from the pair's first corner, so that the rounding
+                // is that of the pair's extent
+                Tt a[9], b[9], u[3], uu = 0, amax = 0, bmin = 0;
+#pragma unroll
+                for (int k = 0; k < 9; k++) {
+                    const Tt o = PREC == 0 ? (Tt)0 : pa[k % 3];
+                    a[k] = pa[k] - o;
+                    b[k] = pb[k] - o;
+                }
 #pragma unroll
                 for (int k = 0; k < 3; k++) {
-                    u[k] = (pb[k] + pb[3 + k] + pb[6 + k]) - (pa[k] + pa[3 + k] + pa[6 + k]);
+                    u[k] = (b[k] + b[3 + k] + b[6 + k]) - (a[k] + a[3 + k] + a[6 + k]);
                     uu += u[k] * u[k];
                 }
 #pragma unroll
                 for (int k = 0; k < 3; k++) {
-                    const Tt x = u[0] * pa[3 * k] + u[1] * pa[3 * k + 1] + u[2] * pa[3 * k + 2];
-                    const Tt y = u[0] * pb[3 * k] + u[1] * pb[3 * k + 1] + u[2] * pb[3 * k + 2];
+                    const Tt x = u[0] * a[3 * k] + u[1] * a[3 * k + 1] + u[2] * a[3 * k + 2];
+                    const Tt y = u[0] * b[3 * k] + u[1] * b[3 * k + 1] + u[2] * b[3 * k + 2];
                     amax = k == 0 ? x : fmax(amax, x);
                     bmin = k == 0 ? y : fmin(bmin, y);
                 }
