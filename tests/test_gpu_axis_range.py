@@ -1,6 +1,7 @@
 """The separating-axis culls of the triangle-pair pass where their arithmetic
 leaves its range: rows far from the origin (the FP64 corners are absolute
-coordinates, the row's margin only a part of its extent).
+coordinates, the row's margin only a part of its extent), and scales at which
+products of FP32 coordinates overflow.
 
 Bar, as for the culls at ordinary scales: flags exact, distances within
 2e-12 d + 32 u S of the oracle's (twice the FP64 error model of a pair
@@ -84,3 +85,32 @@ def test_single_rows_far_from_the_origin(ctx):
     A, B = _far_rows(3)
     for i in range(72, 144, 5):  # (calls of one row bound it by other kernels)
         _check(ctx, A[i:i + 1], B[i:i + 1], 0)
+
+
+def _scale_rows(s):
+    """Gaps well below the bodies' size, off the centre of their tile: corners
+    in the frame of a tile are some 2^0 s, the separations of single pairs
+    some 2^-5 s to 2^-1 s."""
+    t = np.array([[0, 0, 1], [0.1, 0, 1], [0, 0.1, 1]])
+    two = (np.vstack([t, t * [1, 1, -1]]), np.array([[0, 1, 2], [3, 4, 5]], np.int32))
+    A, B = [], []
+    for gap in (0.05, 0.1, 0.2, 0.3, 0.6):
+        A.append(two)
+        B.append((t + [0, 0, gap], TRI1))
+    x, f = synth.icosphere(2)
+    A += [(x, f)] * 3
+    B += [(x * 1.03125, f), (x[f[0]] * 1.015625, TRI1), synth.blob(500, 0.8, (1.7, 0.9, 0.2), 1)]
+    return [(x * s, f) for x, f in A], [(x * s, f) for x, f in B]
+
+
+# every product of two corners leaves FP32's range near 2^64, every corner
+# near 2^128
+@pytest.mark.parametrize("tile", [32, 64, 128])
+@pytest.mark.parametrize("lo,hi,step", [(58.0, 68.0, 0.25), (119.0, 127.0, 0.5), (-50.0, -40.0, 2.0)])
+def test_scales(ctx, lo, hi, step, tile):
+    A, B = [], []
+    for e in np.arange(lo, hi + step, step):
+        a, b = _scale_rows(2.0 ** e)
+        A += a
+        B += b
+    _check(ctx, A, B, tile)
