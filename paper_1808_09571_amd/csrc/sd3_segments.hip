@@ -456,9 +456,9 @@ constexpr float CULL_EPS = 0x1p-18f;
 // segment, |p - x|^2 >= |p - c|^2 - 2 |h| w - 2 l r + r^2 (h = n . (p - c), l
 // the part of p - c across n, r = |y| <= rho): the segment's smallest |p - c|
 // and its largest |h| and l (attained at an end) bound it.  Where both ends
-// are on one side of the cylinder, (min |h| - w)^2 does too.  NaN (a segment
-// beyond FP32's range of the mesh) culls nothing.  d2: the squared distance
-// to c, up: that plus the allowance.
+// are on one side of the cylinder, (min |h| - w)^2 does too.  A segment beyond
+// FP32's range of the mesh is NaN, so are its bounds, and these cull nothing.
+// d2: the squared distance to c, up: that plus the allowance.
 __device__ __forceinline__ float node_bound2(const SegF &s, const float4 &a, const float4 &b, float &up) {
     float r0[3], r1[3];
     const float d2 = seg_point2(s, a, r0, r1);
@@ -489,8 +489,9 @@ __device__ __forceinline__ float node_bound2(const SegF &s, const float4 &a, con
 // With M the largest coordinate of the segment's ends and e = 2^-24, rounding
 // into the frame moves the points by at most e sqrt(3) (3 M + 1), the vector
 // and the separation (differences, three products, the quotient) add at most
-// 40 e (3 M + 1) in all; 128 e (M + 1) is allowed.  NaN (a segment beyond
-// FP32's range of the mesh) bounds nothing.
+// 40 e (3 M + 1) in all; 128 e (M + 1) is allowed.  A segment that is NaN
+// (beyond FP32's range of the mesh) has no candidate: ub is +inf, lb (+inf
+// times rsq(+inf) = 0) NaN, and neither decides anything.
 struct SegBound {
     float ub, lb;
 };
@@ -642,10 +643,15 @@ __global__ __launch_bounds__(64, 3) void k_segs(const double *seg, int64_t n, co
                     u[c] *= t1 - t0;
                 }
             }
+            // a segment with an end beyond 2^56 frame units is NaN: its FP32
+            // products could overflow one by one, which would leave bounds
+            // that look like any other
+            double far = 0.0;
+            for (int c = 0; c < 3; c++) far = fmax(far, fmax(fabs(p[c]), fabs(p[c] + u[c])));
             float q = 0.0f;
             for (int c = 0; c < 3; c++) {
-                me.p[c] = (float)p[c];
-                me.u[c] = (float)u[c];
+                me.p[c] = far < 0x1p56 ? (float)p[c] : __builtin_nanf("");
+                me.u[c] = far < 0x1p56 ? (float)u[c] : __builtin_nanf("");
                 q = fmaf(me.u[c], me.u[c], q);
             }
             me.iu = q > 0.0f ? 1.0f / q : 0.0f;
