@@ -102,6 +102,7 @@ __device__ __forceinline__ DD vol_term(const double (&p)[3][3]) {
 constexpr int VOL_CHUNK = 4096;  // triangles per work item
 constexpr int VOL_WG = 256;
 constexpr int VOL_BATCH = 4;     // triangles a thread loads at once
+constexpr int64_t VOL_SLICE = 1 << 23;  // items per launch
 
 // Items per row: its triangle chunks, and one for a row of vertices alone.
 __host__ __device__ __forceinline__ int64_t vol_row_items(int64_t nt, int64_t nv) {
@@ -114,15 +115,15 @@ __device__ __forceinline__ uint32_t vol_coord(double v) {
     return x != 0.0 && (x < 0x1p-256 || x > 0x1p256) ? V_RANGE : 0u;
 }
 
-// One block per item (witem[g]: row g's first item).
+// One block per item from `first` on (witem[g]: row g's first item).
 __global__ __launch_bounds__(VOL_WG) void k_vol_partial(const double *xyz, const int32_t *tri,
                                                         const int64_t *v_off, const int64_t *t_off,
-                                                        const int64_t *witem, int64_t G, DD *part,
+                                                        const int64_t *witem, int64_t first, int64_t G, DD *part,
                                                         uint32_t *flags) {
     __shared__ DD red[VOL_WG / 64];
     // consecutive items to one XCD (workgroups are dealt to the eight in turn)
     const unsigned x = blockIdx.x & 7u, nq = gridDim.x >> 3, nr = gridDim.x & 7u;
-    const int64_t it = (int64_t)x * nq + min(x, nr) + (blockIdx.x >> 3);
+    const int64_t it = first + (int64_t)x * nq + min(x, nr) + (blockIdx.x >> 3);
     int64_t lo = 0, hi = G;  // the row, found by the wave: 64 probes a round
     while (hi - lo > 1) {
         const int64_t step = (hi - lo + 63) >> 6;
@@ -205,9 +206,10 @@ void launch_volume(const double *xyz, const int32_t *tri, const int64_t *v_off, 
                    int64_t nitems, const int64_t *witem, int64_t G, void *part, double *vol, uint32_t *flags,
                    hipStream_t s) {
     hipLaunchKernelGGL(k_vol_clear, dim3(1), dim3(64), 0, s, flags);
-    if (nitems > 0)
-        hipLaunchKernelGGL(k_vol_partial, dim3((unsigned)nitems), dim3(VOL_WG), 0, s, xyz, tri, v_off, t_off, witem,
-                           G, (DD *)part, flags);
+    // (a launch takes fewer than 2^32 threads)
+    for (int64_t i0 = 0; i0 < nitems; i0 += VOL_SLICE)
+        hipLaunchKernelGGL(k_vol_partial, dim3((unsigned)std::min(nitems - i0, VOL_SLICE)), dim3(VOL_WG), 0, s, xyz, tri,
+                           v_off, t_off, witem, i0, G, (DD *)part, flags);
     if (G > 0)
         hipLaunchKernelGGL(k_vol_rows, dim3((unsigned)((G + 63) / 64)), dim3(64), 0, s, (const DD *)part, witem, G,
                            vol, flags);
