@@ -574,7 +574,9 @@ void plan_call(sd3_ctx *ctx, Workspace &ws, const sd3_geoms *a, const sd3_geoms 
         C.PB.cub = cull && mode == 0 ? (double *)ws.buf(ws.cub, sizeof(double) * G) : nullptr;
         C.PB.oc = cull ? (uint8_t *)ws.buf(ws.oc, (size_t)(C.A.nv + C.B.nv)) : nullptr;
         C.PB.local = P.rsi == RS_ITEMS && P.max_row <= RS_ITEMS;
-        C.PB.local_box = C.PB.local && P.max_verts <= ROWBOX_ROW;
+        // (a block per row and side: at most 2^32 threads a launch, and no
+        // blocks for the empty rows of a sparse column)
+        C.PB.local_box = C.PB.local && P.max_verts <= ROWBOX_ROW && G <= ROWBOX_MAX_ROWS && G <= C.A.nv + C.B.nv;
         C.PB.seg = SortSeg{ds + 9 * G1, ds + 10 * G1, C.A.t_off, C.B.t_off, G, C.A.nt, P.sbA[G], nb, P.rsi,
                            G >= SORT_TABLE_MIN_ROWS && !C.PB.local ? (SBlock *)ws.buf(ws.sorttab, sizeof(SBlock) * (nb + 1))
                                                     : nullptr,

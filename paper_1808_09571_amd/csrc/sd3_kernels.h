@@ -81,6 +81,8 @@ struct SortSeg {
 };
 // Vertices of a row that one block reduces to its box.
 constexpr int64_t ROWBOX_ROW = 8192;
+// Rows of one such launch (two blocks of 256 threads each).
+constexpr int64_t ROWBOX_MAX_ROWS = 1 << 22;
 // Calls of at least this many rows build the sort-block table first.
 constexpr int64_t SORT_TABLE_MIN_ROWS = 64;
 
@@ -101,7 +103,7 @@ struct PrepBufs {
                         // (intersects culls by the box itself)
     SortSeg seg;
     bool local;         // every row fits one sort block: keys and sort in one launch
-    bool local_box;     // and has at most ROWBOX_ROW vertices a side: a block per row box
+    bool local_box;     // and has at most ROWBOX_ROW vertices a side, the call few empty rows: a block per row box
     uint32_t *flags;    // [2] validation flags of A and B (the key kernel checks indices)
 };
 

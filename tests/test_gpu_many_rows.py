@@ -44,3 +44,27 @@ def test_volume_of_2_24_rows(ctx):
     assert torch.equal(v[torch.tensor(at, device="cuda:0")], alone)
     v[torch.tensor(at, device="cuda:0")] = 0.0
     assert not bool(v.any())
+
+
+def test_distance_of_a_sparse_column_of_2_23_rows(ctx):
+    import torch
+    # three rows of bodies, every other row empty on both sides
+    n = (1 << 23) + 3
+    at = np.array([0, n // 2, n - 1])
+    A, B = zip(*(synth.config_icospheres(k) for k in range(3)))
+
+    def sparse(meshes):
+        p = synth.pack(list(meshes))
+        nv, nt = np.zeros(n, np.int64), np.zeros(n, np.int64)
+        nv[at], nt[at] = np.diff(p.v_off), np.diff(p.t_off)
+        b = sd3.Batch.from_packed(p, "cuda:0")
+        return b, sd3.Batch(b.xyz, b.tri, *(np.concatenate([[0], np.cumsum(c)]) for c in (nv, nt)))
+
+    (a3, a), (b3, b) = sparse(A), sparse(B)
+    d, h = ctx.distance(a, b)
+    d3, h3 = ctx.distance(a3, b3)
+    rows = torch.from_numpy(at).to("cuda:0")
+    assert torch.equal(d[rows], d3) and torch.equal(h[rows], h3)
+    d[rows] = float("inf")
+    h[rows] = 0
+    assert bool(torch.isinf(d).all()) and not bool(h.any())
