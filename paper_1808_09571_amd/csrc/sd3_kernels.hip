@@ -2375,6 +2375,12 @@ struct Entry {
     double eps_c;
 };
 
+// elb is at least 16 sqrt(3) 2^-24 of the largest corner component M of a tile
+// pair, so below this M < 2^59.3 and a sum u of six corners has |u|^2 < 2^126:
+// no product of the axis culls overflows.  Tile pairs above it get elb = +inf,
+// which separates nothing and sends every pair tested to the FP64 rescue.
+constexpr float AXIS_ELB = 0x1p40f;
+
 // Gathers entry q0 + lane of the batch in lane `lane` (lanes at
 // and beyond the batch size keep ta = -1).  In the seed pass entry g is row
 // g's chosen queue entry.  Returns 1 in the lanes whose two tiles name
@@ -2433,7 +2439,7 @@ __device__ __forceinline__ int wave_gather(Entry &E, const Lists &L, unsigned qc
                 E.sh1 = c.sh[1];
                 E.sh2 = c.sh[2];
                 E.eu = c.eu;
-                E.elb = c.elb;
+                E.elb = MODE == 0 && c.elb >= AXIS_ELB ? __builtin_inff() : c.elb;
                 E.eps_f = c.eps_f;
                 E.box_tol = c.box_tol;
                 E.eps_c = c.eps_c;
@@ -2455,11 +2461,8 @@ __device__ __forceinline__ double fp32_upper(float dm, float eu) {
 // with elb bounding the copies' distance from the real points plus the
 // rounding (at most sqrt(3) * 8 roundings of the largest offset here, elb
 // holds 16).  A direction too short for its square to keep full precision
-// decides nothing.  Corners must be below AXIS_ELB's bound: an overflow in u . p
-// would look like any separation (and fmin and fmax drop a NaN).
-// elb is at least 16 sqrt(3) 2^-24 of the largest corner component M of a tile
-// pair, so below this M < 2^59.3, u (six corners) < 2^62, |u|^2 < 2^126.
-constexpr float AXIS_ELB = 0x1p40f;
+// decides nothing.  (An overflow in u . p would look like any separation, and
+// fmin and fmax drop a NaN: where one could occur, elb is +inf.)
 __device__ __forceinline__ bool axis_far32(float sep, float uu, float elb, float limf) {
     return uu >= 0x1p-120f && sep * __builtin_amdgcn_rsqf(uu) - elb > limf;
 }
@@ -2630,7 +2633,7 @@ __global__ __launch_bounds__(64, PREC == 0 && TK <= 64 ? 3 : 1) void k_pairs(con
                     const double T = (ub + m + eps_c) / (1.0 - 4.0 * U32);
                     const double T2 = T * T * (1.0 + 16.0 * U32);
                     T2f = T2 < 3.0e38 ? (float)(T2 * (1.0 + 0x1p-20)) : __builtin_inff();
-                    limf = elb < AXIS_ELB ? (float)((ub + m) * (1.0 + 0x1p-20)) : __builtin_inff();
+                    limf = (float)((ub + m) * (1.0 + 0x1p-20));
                 } else {
                     const double T = (ub + m) * (1.0 + 8.0 * U64);
                     T2d = T * T;
