@@ -179,7 +179,8 @@ __device__ __forceinline__ uint32_t coord_flags(double v) {
 
 // Validation of the segment coordinates (flags[0]) and of the mesh
 // (coordinates and indices, flags[1]), and the mesh's box (ordered bits) from
-// its vertices; k_seg_clear set every word.  The first blocks, one per run, put
+// its triangles' corners (a vertex that none uses must not widen the frame:
+// what FP32 tells apart is a part of it); k_seg_clear set every word.  The first blocks, one per run, put
 // the mesh's triangles in order meanwhile: the sort of a small mesh is a chain
 // of waits in one block that no other work needs yet.
 __global__ __launch_bounds__(1024) void k_seg_validate(const double *seg, int64_t n, const double *xyz,
@@ -205,22 +206,24 @@ __global__ __launch_bounds__(1024) void k_seg_validate(const double *seg, int64_
         for (int k = 0; k < 8; k++) fs |= coord_flags(x[k]);
     }
     for (; i0 < 6 * n; i0 += stride) fs |= coord_flags(seg[i0]);
+    for (int64_t i = first; i < 3 * nv; i += stride) fm |= coord_flags(xyz[i]);
     double lo[3] = {__builtin_inf(), __builtin_inf(), __builtin_inf()};
     double hi[3] = {-__builtin_inf(), -__builtin_inf(), -__builtin_inf()};
-    for (int64_t i = first; i < nv; i += stride)
-        for (int c = 0; c < 3; c++) {
-            const double v = xyz[3 * i + c];
-            fm |= coord_flags(v);
-            lo[c] = fmin(lo[c], v);
-            hi[c] = fmax(hi[c], v);
-        }
     for (int64_t i = first; i < 3 * nt; i += stride) {
         const int32_t v = tri[i];
-        if (v < 0 || (int64_t)v >= nv) fm |= V_INDEX;
+        if (v < 0 || (int64_t)v >= nv) {
+            fm |= V_INDEX;
+            continue;
+        }
+        for (int c = 0; c < 3; c++) {
+            const double x = xyz[3 * (int64_t)v + c];
+            lo[c] = fmin(lo[c], x);
+            hi[c] = fmax(hi[c], x);
+        }
     }
     if (fs) atomicOr(&flags[0], fs);
     if (fm) atomicOr(&flags[1], fm);
-    if (block * (int64_t)blockDim.x >= nv) return;  // (block-uniform)
+    if (block * (int64_t)blockDim.x >= 3 * nt) return;  // (block-uniform)
     for (int c = 0; c < 3; c++) {
         const double a = wave_min(lo[c]), b = wave_max(hi[c]);
         if (lane_id() == 0) {

@@ -60,3 +60,23 @@ def test_longest_segments(ctx, size):
         do, ho, _ = oracle.mesh((np.array([p, q, q]), TRI1), (x, t))
         assert bool(h[i]) == ho and bool(hi[i]) == ho and bool(w[i]) == (d[i] <= 0.25), i
         assert abs(d[i] - do) <= 2e-12 * do + 32 * 2.0 ** -53 * 4.2 * 2.0 ** size, (i, d[i], do)
+
+
+@pytest.mark.parametrize("far", [10.0, 1e3, 1e9])
+def test_vertices_of_no_triangle(ctx, far):
+    # a vertex that no triangle uses changes nothing: not the results, nor how
+    # many triangles are compared
+    import torch
+    x, t = synth.icosphere(3)
+    g = np.random.default_rng(2)
+    p = g.uniform(-1.5, 1.5, size=(500, 3))
+    seg = np.stack([p, p + g.normal(size=(500, 3)) * 0.3], axis=1)
+    sg = torch.from_numpy(seg).to("cuda:0")
+    out = []
+    for y in (x, np.vstack([x, [[far, -far, 0.0]]])):
+        mb = sd3.Batch.from_packed(synth.pack([(y, t)]), "cuda:0")
+        for op in ("distance", "intersects", "within"):
+            r, st = ctx.segments(op, sg, mb, r=0.1, stats=True)
+            out.append((r if op == "distance" else (r,), st["tri_pairs_boxed"], st["tri_pairs_fp64"]))
+    for a, b in zip(out[:3], out[3:]):
+        assert all(torch.equal(u, v) for u, v in zip(a[0], b[0])) and a[1:] == b[1:]
