@@ -80,3 +80,18 @@ def test_vertices_of_no_triangle(ctx, far):
             out.append((r if op == "distance" else (r,), st["tri_pairs_boxed"], st["tri_pairs_fp64"]))
     for a, b in zip(out[:3], out[3:]):
         assert all(torch.equal(u, v) for u, v in zip(a[0], b[0])) and a[1:] == b[1:]
+
+
+def test_exact_tests_of_long_segments(ctx):
+    # intersects settles near misses without exact arithmetic as distance does
+    import torch
+    x, t = synth.icosphere(4)
+    g = np.random.default_rng(1)
+    u = g.normal(size=(500, 3))
+    u /= np.linalg.norm(u, axis=1)[:, None]
+    a = g.uniform(-1.2, 1.2, size=(500, 3))
+    sg = torch.from_numpy(np.stack([a - 2e6 * u, a + 2e6 * u], axis=1)).to("cuda:0")
+    mb = sd3.Batch.from_packed(synth.pack([(x, t)]), "cuda:0")
+    (_, h), sd = ctx.segments("distance", sg, mb, stats=True)
+    f, si = ctx.segments("intersects", sg, mb, stats=True)
+    assert torch.equal(h, f) and si["exact"] <= 2 * sd["exact"], (si["exact"], sd["exact"])
