@@ -165,11 +165,12 @@ typedef struct sd3_stats {
        building, [2] tile-pair box filter, [3] main triangle-pair pass */
     double ms_kernel[4];
     int64_t n_kernel[4];
-    int64_t sort_items;            /* keys per radix pass (both sides) */
+    int64_t sort_items;            /* keys sorted (both sides) */
     int32_t sort_item_bytes;       /* bytes an item moves through the radix
                                       scatter passes (read and written,
                                       summed over the passes) */
-    int32_t sort_passes;
+    int32_t sort_passes;           /* scatter passes (0, as the bytes: small
+                                      rows, sorted without any) */
     int32_t tile;                  /* triangles per tile used by the call */
     int32_t queue_passes;          /* candidate-queue passes */
     int64_t queue_skew;            /* consistency check of the tile-pair pass:

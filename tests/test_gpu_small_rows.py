@@ -93,3 +93,11 @@ def test_small_rows_refuse_bad_contents(ctx):
             with pytest.raises(sd3.SD3Error) as e:
                 ctx.distance(*(rows if side == 0 else rows[::-1]))
             assert e.value.name == name
+
+
+@pytest.mark.parametrize("nt", [2048, 2049])
+def test_stats_report_the_scatter_passes_that_ran(ctx, nt):
+    a, b = _batch([_soup(nt, 1)]), _batch([_soup(9, 2)])
+    _, _, st = ctx.distance(a, b, stats=True, timing=True)
+    assert st["sort_passes"] == st["n_kernel"]["scatter"] == (0 if nt <= 2048 else 2)
+    assert st["sort_item_bytes"] == (0 if nt <= 2048 else 20) and st["sort_items"] == nt + 9
