@@ -1796,10 +1796,11 @@ struct WorkItem {
     bool bvalid;
 };
 
-__device__ __forceinline__ WorkItem decode_item(const int64_t *wi_off, int64_t G, int64_t wi,
+// (g: the item's row)
+__device__ __forceinline__ WorkItem decode_item(const int64_t *wi_off, int64_t g, int64_t wi,
                                                 const int64_t *tA, const int64_t *tB) {
     WorkItem w;
-    w.g = find_row(wi_off, G, wi);
+    w.g = g;
     int64_t local = wi - wi_off[w.g];
     int64_t nA = tA[w.g + 1] - tA[w.g], nB = tB[w.g + 1] - tB[w.g];
     int64_t nbc = (nB + 255) / 256;
@@ -1943,7 +1944,9 @@ __global__ void k_wi_compact(const float *wi_lb, const int64_t *wi_off, int64_t 
     if (keep) list[base + __popcll(m & lanes_below())] = (int32_t)wi;
 }
 
-// The work items a block takes.  Over the compacted list: its one entry.
+// The work items a block takes, with their rows.  Over the compacted list
+// (LIST): its one entry, whose row a wave finds (a search by every thread, and
+// a second one to check the bound: k_ub_seed of 200,000 rows 1089 -> 389 us).
 // Without a list (calls of few rows): up to WI_PER of the pass's n_wi items, a
 // grid apart (survivors lie side by side), those whose group bound still
 // holds; one wave looks them all up at once, so that a large pair's pruned
@@ -1953,36 +1956,44 @@ __global__ void k_wi_compact(const float *wi_lb, const int64_t *wi_off, int64_t 
 // other workgroups lower them, and every thread must take the same branches.
 constexpr int WI_PER = 16;
 struct WorkList {
-    int32_t item[WI_PER];
+    int32_t item[WI_PER], row[WI_PER];
     int n;
 };
+template <bool LIST>
 __device__ __forceinline__ void block_items(WorkList &W, const int32_t *wlist, const unsigned int *wcount,
                                             int64_t wi0, int64_t n_wi, const float *wi_lb, const int64_t *wi_off,
                                             int64_t G, const RowState *rows, int mode) {
     if (threadIdx.x < 64) {
         const int k = (int)threadIdx.x;
         bool keep = false;
-        int64_t wi = 0;
-        if (wlist) {
-            keep = k == 0 && blockIdx.x < *wcount;
-            if (keep) wi = wlist[blockIdx.x];
+        int64_t wi = 0, g = 0;
+        if (LIST) {
+            if (blockIdx.x < *wcount) {  // (wave-uniform)
+                wi = wlist[blockIdx.x];
+                g = wave_find_row(wi_off, G, wi);
+                keep = k == 0;
+            }
         } else {
             const int64_t at = (int64_t)blockIdx.x + (int64_t)k * gridDim.x;
             keep = k < WI_PER && at < n_wi;
             wi = wi0 + at;
+            if (keep) g = find_row(wi_off, G, wi);
         }
         if (keep) {
             const double lb = (double)wi_lb[wi];
             if (mode == 1) {
                 keep = lb <= 0.0;
             } else {
-                const RowState &R = rows[find_row(wi_off, G, wi)];
+                const RowState &R = rows[g];
                 const double ub = bits_to_double(load_acq(&R.ub));
                 keep = lb <= ub + row_margin(R, ub);
             }
         }
         const unsigned long long m = __ballot(keep);
-        if (keep) W.item[__popcll(m & lanes_below())] = (int32_t)wi;
+        if (keep) {
+            W.item[__popcll(m & lanes_below())] = (int32_t)wi;
+            W.row[__popcll(m & lanes_below())] = (int32_t)g;
+        }
         if (k == 0) W.n = __popcll(m);
     }
     __syncthreads();
@@ -1995,6 +2006,7 @@ static unsigned wi_blocks(int64_t n_wi) {
 
 // Upper bound seed: the distance between two real vertices bounds the row
 // distance from above.  Over the compacted list (wlist) or every work item.
+template <bool LIST>
 __global__ __launch_bounds__(256) void k_ub_seed(const TileMeta *mA, const TileMeta *mB,
                                                  const int64_t *tA, const int64_t *tB,
                                                  const int64_t *wi_off, int64_t G,
@@ -2003,10 +2015,10 @@ __global__ __launch_bounds__(256) void k_ub_seed(const TileMeta *mA, const TileM
     __shared__ double rep[64][3];
     __shared__ double wred[4];
     __shared__ WorkList W;
-    block_items(W, wlist, wcount, 0, n_wi, wi_lb, wi_off, G, rows, 0);
+    block_items<LIST>(W, wlist, wcount, 0, n_wi, wi_lb, wi_off, G, rows, 0);
     for (int li = 0; li < W.n; li++) {
         if (li > 0) __syncthreads();
-        WorkItem w = decode_item(wi_off, G, W.item[li], tA, tB);
+        WorkItem w = decode_item(wi_off, W.row[li], W.item[li], tA, tB);
         if (threadIdx.x < w.na)
             for (int k = 0; k < 3; k++) rep[threadIdx.x][k] = mA[w.a0 + threadIdx.x].rep[k];
         __syncthreads();
@@ -2044,7 +2056,7 @@ __device__ __forceinline__ uint32_t float_order_bits(float f) {
 // each row's seed: the kept entry with the smallest box bound, combined per
 // wave and published with one atomicMin per wave on the row's choice (ordered
 // bound bits << 32 | queue index).
-template <int RANK>
+template <int RANK, bool LIST>
 __global__ __launch_bounds__(256) void k_filter(const TileMeta *mA, const TileMeta *mB,
                                                 const int64_t *tA, const int64_t *tB,
                                                 const int64_t *wi_off, int64_t G, int64_t wi0,
@@ -2058,10 +2070,10 @@ __global__ __launch_bounds__(256) void k_filter(const TileMeta *mA, const TileMe
     // block 0 of the first uncompacted pass also sets the rows' feature scale
     if (scale_rows && blockIdx.x + blockIdx.y == 0)
         for (int64_t g = threadIdx.x; g < G; g += blockDim.x) row_scale(scale_rows, g);
-    block_items(W, wlist, wcount, wi0, n_wi, wi_lb, wi_off, G, rows, mode);
+    block_items<LIST>(W, wlist, wcount, wi0, n_wi, wi_lb, wi_off, G, rows, mode);
     for (int li = 0; li < W.n; li++) {
         if (li > 0) __syncthreads();
-        WorkItem w = decode_item(wi_off, G, W.item[li], tA, tB);
+        WorkItem w = decode_item(wi_off, W.row[li], W.item[li], tA, tB);
         if (threadIdx.x < w.na)
             for (int k = 0; k < 3; k++) {
                 box[threadIdx.x][k] = mA[w.a0 + threadIdx.x].lo[k];
@@ -2150,7 +2162,7 @@ static void launch_filter(const SideBufs &A, const SideBufs &B, const QueueGeo &
         hipLaunchKernelGGL(k_wi_compact, dim3(grid_for(nthreads, 256)), dim3(256), 0, s, Q.wi_lb,
                            Q.wi_off, A.G, n_wi, rows, mode, Q.wlist, Q.wcount + 1,
                            mode == 0 ? rows : (RowState *)nullptr);
-        hipLaunchKernelGGL(k_filter<RANK>, dim3(nb), dim3(256), 0, s, A.meta, B.meta, A.tile_off,
+        hipLaunchKernelGGL((k_filter<RANK, true>), dim3(nb), dim3(256), 0, s, A.meta, B.meta, A.tile_off,
                            B.tile_off, Q.wi_off, A.G, (int64_t)0, rows, mode, L.queue, L.qlb,
                            L.qcount, L.qcap, Q.wi_lb, Q.wlist, Q.wcount + 1, n_wi,
                            (RowState *)nullptr);
@@ -2158,7 +2170,7 @@ static void launch_filter(const SideBufs &A, const SideBufs &B, const QueueGeo &
         // few work items survive in a call of few rows, and the loop over 64 A
         // tiles is its time: four blocks share an item's (TIN pair of
         // 512 x 512 cells 16.9 -> 12.1 us, an icosphere pair 10.2 -> 8.2)
-        hipLaunchKernelGGL(k_filter<RANK>, dim3(wi_blocks(n_wi), 4), dim3(256), 0, s, A.meta, B.meta, A.tile_off,
+        hipLaunchKernelGGL((k_filter<RANK, false>), dim3(wi_blocks(n_wi), 4), dim3(256), 0, s, A.meta, B.meta, A.tile_off,
                            B.tile_off, Q.wi_off, A.G, wi_begin, rows, mode, L.queue, L.qlb,
                            L.qcount, L.qcap, Q.wi_lb, (const int32_t *)nullptr,
                            (const unsigned int *)nullptr, n_wi,
@@ -2177,10 +2189,10 @@ void launch_queue(const SideBufs &A, const SideBufs &B, const QueueGeo &Q, int64
         if (what == Q_SEED && Q.compact) {
             hipLaunchKernelGGL(k_wi_compact, dim3(grid_for(n_wi, 256)), dim3(256), 0, s, Q.wi_lb,
                                Q.wi_off, A.G, n_wi, rows, 0, Q.wlist, Q.wcount, (RowState *)nullptr);
-            hipLaunchKernelGGL(k_ub_seed, dim3(nb), dim3(256), 0, s, A.meta, B.meta, A.tile_off,
+            hipLaunchKernelGGL(k_ub_seed<true>, dim3(nb), dim3(256), 0, s, A.meta, B.meta, A.tile_off,
                                B.tile_off, Q.wi_off, A.G, rows, Q.wi_lb, Q.wlist, Q.wcount, n_wi);
         } else if (what == Q_SEED) {
-            hipLaunchKernelGGL(k_ub_seed, dim3(wi_blocks(n_wi)), dim3(256), 0, s, A.meta, B.meta, A.tile_off,
+            hipLaunchKernelGGL(k_ub_seed<false>, dim3(wi_blocks(n_wi)), dim3(256), 0, s, A.meta, B.meta, A.tile_off,
                                B.tile_off, Q.wi_off, A.G, rows, Q.wi_lb, (const int32_t *)nullptr,
                                (const unsigned int *)nullptr, n_wi);
         }
