@@ -829,6 +829,10 @@ __global__ __launch_bounds__(1024) void k_morton(MortonSide A, MortonSide B, Sor
     if (VC && M.kc && threadIdx.x == 0 && nkeep) atomicAdd(M.kc + k.g, (int32_t)nkeep);
 }
 
+// Items up to which counting lower words beats the two passes (5000 pairs of 320
+// triangles: 0.30 ms counting, 0.19 the passes).
+constexpr int LOCAL_RANK = 128;
+
 // Keys and sort in one launch where no row has more triangles than a sort
 // block (two passes of 8 bits): every row is one block per side, whose items
 // take their places inside it, so no histogram leaves the block.  The key is
@@ -881,17 +885,23 @@ __global__ __launch_bounds__(1024) void k_local_sort(MortonSide A, MortonSide B,
     unsigned long long b[6];
     for (int c = 0; c < 6; c++) b[c] = __shfl(mb, c);
     const double sc = row_cells(b, lo);
-    if (k.n <= 64) {
-        // (block-uniform) one wave holds the items, and an item's place is the
-        // number of lower words: the passes' counters and barriers would be
-        // all that a column of very small rows costs (200,000 pairs of 4
-        // triangles: 7.12 -> 3.55 ms here, 6.85 in the general path's launches)
-        if (threadIdx.x < 64) {
-            const uint32_t w = (morton_code(p[0], lo, sc) >> 14) << 16 | (uint32_t)lane;
-            int at = 0;
-            for (int j = 0; j < k.n; j++) at += (uint32_t)__builtin_amdgcn_readlane((int)w, j) < w;
-            if (lane < k.n) out[k.i0 + at] = (uint32_t)lane;
+    if (k.n <= LOCAL_RANK) {
+        // (block-uniform) an item's place is the number of lower words: the
+        // passes' counters and barriers would be all that a column of very
+        // small rows costs (200,000 pairs of 4 triangles: 7.12 -> 3.90 ms
+        // here, 6.85 in the general path's launches; 20,000 of 80: 0.73 -> 0.57)
+        const int tid = (int)threadIdx.x;
+        const uint32_t w = (morton_code(p[0], lo, sc) >> 14) << 16 | (uint32_t)tid;
+        if (tid < k.n) L.a[tid] = w;
+        __syncthreads();
+        if ((tid & ~63) >= k.n) return;
+        int at = 0;
+        for (int c = 0; c < k.n; c += 64) {
+            const uint32_t x = L.a[min(c + lane, k.n - 1)];
+            const int m = min(64, k.n - c);
+            for (int j = 0; j < m; j++) at += (uint32_t)__builtin_amdgcn_readlane((int)x, j) < w;
         }
+        if (tid < k.n) out[k.i0 + at] = (uint32_t)tid;
         return;
     }
 #pragma unroll

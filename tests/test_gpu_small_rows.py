@@ -101,3 +101,20 @@ def test_stats_report_the_scatter_passes_that_ran(ctx, nt):
     _, _, st = ctx.distance(a, b, stats=True, timing=True)
     assert st["sort_passes"] == st["n_kernel"]["scatter"] == (0 if nt <= 2048 else 2)
     assert st["sort_item_bytes"] == (0 if nt <= 2048 else 20) and st["sort_items"] == nt + 9
+
+
+def test_rows_ranked_by_counting_equal_the_general_path(ctx):
+    # up to 128 triangles a row; fans share their first vertices, so that every
+    # key of the row is the same
+    A, B = [], []
+    for n in (3, 127, 128, 129, 190):
+        x, t = _soup(n, n)
+        A += [(x, t), (x, np.stack([np.full(n, t[0, 0]), t[:, 1], t[:, 2]], axis=1).astype(np.int32))]
+        B += [_soup(131 - n % 3, n + 1, center=(1.3, 0.2, 0.1))] * 2
+    d, h = ctx.distance(_batch(A), _batch(B))
+    dg, hg = ctx.distance(_batch(A + [_soup(2049, 99)]), _batch(B + [_soup(3, 1)]))
+    assert np.array_equal(d.cpu().numpy(), dg.cpu().numpy()[:len(A)])
+    assert np.array_equal(h.cpu().numpy(), hg.cpu().numpy()[:len(A)])
+    for i in range(len(A)):
+        do, ho, _ = oracle.mesh(A[i], B[i])
+        assert bool(h[i]) == ho and abs(float(d[i]) - do) <= 1e-12 * do
