@@ -1250,8 +1250,12 @@ sd3_status sd3_volume(sd3_ctx *ctx, const sd3_geoms *g, double *vol, sd3_stats *
         memcpy(h_voff, g->v_off, sizeof(int64_t) * (G + 1));
         memcpy(h_toff, g->t_off, sizeof(int64_t) * (G + 1));
         h_witem[0] = 0;
-        for (int64_t r = 0; r < G; r++)
-            h_witem[r + 1] = h_witem[r] + volume_items(g->t_off[r + 1] - g->t_off[r], g->v_off[r + 1] - g->v_off[r]);
+        int64_t max_row = 0;
+        for (int64_t r = 0; r < G; r++) {
+            const int64_t n = g->t_off[r + 1] - g->t_off[r];
+            h_witem[r + 1] = h_witem[r] + volume_items(n, g->v_off[r + 1] - g->v_off[r]);
+            max_row = std::max(max_row, n);
+        }
         const int64_t nitems = h_witem[G];
         int64_t *d_voff = (int64_t *)ensure(ws.vol_items, bytes + 64);
         check(hipMemcpyAsync(d_voff, h_voff, bytes, hipMemcpyHostToDevice, s), "H2D volume items");
@@ -1273,7 +1277,7 @@ sd3_status sd3_volume(sd3_ctx *ctx, const sd3_geoms *g, double *vol, sd3_stats *
         double *dvol = g->mem == SD3_MEM_HOST ? (double *)((char *)part + 16 * (size_t)(nitems > 0 ? nitems : 1))
                                               : vol;
         unsigned int *sc = (unsigned int *)ensure(ws.scalars, SCALAR_BYTES);
-        launch_volume(xyz, tri, d_voff, d_toff, nitems, d_witem, G, part, dvol, (uint32_t *)sc, s);
+        launch_volume(xyz, tri, d_voff, d_toff, nitems, d_witem, max_row, G, part, dvol, (uint32_t *)sc, s);
         check(hipGetLastError(), "kernel launch");
         char *rb = readback_area(ctx);
         check(hipMemcpyAsync(rb, sc, 4, hipMemcpyDeviceToHost, s), "D2H flags");

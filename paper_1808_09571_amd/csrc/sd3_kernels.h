@@ -291,11 +291,12 @@ void launch_solid_apply(const uint8_t *res, int64_t G, double *dist, uint8_t *hi
 
 // Volume of each row (sd3_volume.hip): a row of nt triangles and nv vertices
 // has volume_items(nt, nv) work items, row g's first is witem[g] (witem[G] =
-// nitems); part holds 16 bytes per item; flags[0] takes the validation bits.
+// nitems), max_row: most triangles of a row; part holds 16 bytes per item;
+// flags[0] takes the validation bits.
 int64_t volume_items(int64_t nt, int64_t nv);
 void launch_volume(const double *xyz, const int32_t *tri, const int64_t *v_off, const int64_t *t_off,
-                   int64_t nitems, const int64_t *witem, int64_t G, void *part, double *vol, uint32_t *flags,
-                   hipStream_t s);
+                   int64_t nitems, const int64_t *witem, int64_t max_row, int64_t G, void *part, double *vol,
+                   uint32_t *flags, hipStream_t s);
 
 // Segments / points against one mesh (sd3_segments.hip).  Mesh preparation:
 // order (the triangles' places along a curve, in runs of RS_ITEMS), P

@@ -111,3 +111,19 @@ def test_chunk_edges(ctx):
         with pytest.raises(sd3.SD3Error) as e:
             _vol(ctx, [meshes[0], lone], dev)
         assert e.value.name == "SD3_E_NONFINITE"
+
+
+def test_columns_of_small_rows_equal_the_general_path(ctx):
+    # rows of at most 256 triangles have a variant of their own: empty rows,
+    # rows of vertices alone, runs of both longer than a round of the search
+    g = np.random.default_rng(6)
+    empty, bare = (np.zeros((0, 3)), np.zeros((0, 3), np.int32)), (g.normal(size=(90, 3)), np.zeros((0, 3), np.int32))
+    meshes = [empty] * 3
+    for k, n in enumerate((1, 2, 63, 64, 65, 128, 255, 256)):
+        x = g.normal(size=(n + 2, 3))
+        meshes += [(x, g.integers(0, n + 2, size=(n, 3)).astype(np.int32))] + [(empty, bare)[k % 2]] * (40 * k)
+    meshes += [synth.cube((0, 0, 0), 1.0)] * 200 + [empty]
+    v = _vol(ctx, meshes, True)
+    longer = _vol(ctx, meshes + [synth.icosphere(2)], True)
+    assert np.array_equal(v.view(np.int64), longer[:-1].view(np.int64)) and v[-2] == 1.0
+    _check(meshes[:40], v[:40])
