@@ -115,13 +115,15 @@ __device__ __forceinline__ uint32_t vol_coord(double v) {
     return x != 0.0 && (x < 0x1p-256 || x > 0x1p256) ? V_RANGE : 0u;
 }
 
-// One block per item from `first` on (witem[g]: row g's first item).  SMALL:
-// no row has more than VOL_WG triangles, so an item is a row, of at most one
-// triangle a thread.  Such columns are bound by each block's chain of loads:
-// the first round of the row's search looks around the place it has where no
-// row is empty, and nothing is loaded for triangles that are not there
-// (200,000 rows of 20 triangles: 862 -> 342 us).
-template <bool SMALL>
+// One block per item from `first` on (witem[g]: row g's first item), a thread
+// loading BATCH triangles at once.  ROWS: no row has more than VOL_CHUNK
+// triangles, so an item is a row.  Such columns are bound by each block's chain
+// of loads, not by the bytes: the first round of the row's search looks around
+// the place it has where no row is empty, and rows of at most 256 or 512
+// triangles load no more a thread than there are (200,000 rows of 20 triangles:
+// 862 -> 342 us; the call on 50,000 rows of 320: 545 -> 400, 30,000 of 720: 407
+// -> 362, 4000 of 3920: 250 -> 245).
+template <int BATCH, bool ROWS>
 __global__ __launch_bounds__(VOL_WG) void k_vol_partial(const double *xyz, const int32_t *tri,
                                                         const int64_t *v_off, const int64_t *t_off,
                                                         const int64_t *witem, int64_t first, int64_t G,
@@ -131,7 +133,7 @@ __global__ __launch_bounds__(VOL_WG) void k_vol_partial(const double *xyz, const
     const unsigned x = blockIdx.x & 7u, nq = gridDim.x >> 3, nr = gridDim.x & 7u;
     const int64_t it = first + (int64_t)x * nq + min(x, nr) + (blockIdx.x >> 3);
     int64_t lo = 0, hi = G;  // the row, found by the wave: 64 probes a round
-    if (SMALL) {
+    if (ROWS) {
         const int64_t q = (int64_t)((double)it * rows_per_item) - 32;
         const int64_t at = q + lane_id();
         const int c = __popcll(__ballot(at <= 0 || (at < G && witem[at] <= it)));
@@ -145,7 +147,7 @@ __global__ __launch_bounds__(VOL_WG) void k_vol_partial(const double *xyz, const
         hi = min(hi, lo + (int64_t)(c + 1) * step);
         lo += (int64_t)c * step;
     }
-    const int64_t g = lo, j = SMALL ? 0 : it - witem[g], items = SMALL ? 1 : witem[g + 1] - witem[g];
+    const int64_t g = lo, j = ROWS ? 0 : it - witem[g], items = ROWS ? 1 : witem[g + 1] - witem[g];
     const int64_t t0 = t_off[g] + j * VOL_CHUNK, t1 = min(t_off[g + 1], t0 + (int64_t)VOL_CHUNK);
     const double *X = xyz + 3 * v_off[g];
     const int64_t nvr = v_off[g + 1] - v_off[g];
@@ -156,7 +158,6 @@ __global__ __launch_bounds__(VOL_WG) void k_vol_partial(const double *xyz, const
 #pragma unroll 4
     for (int64_t i = c0 + threadIdx.x; i < c1; i += VOL_WG) bad |= vol_coord(X[i]);
     DD s = {0.0, 0.0};
-    constexpr int BATCH = SMALL ? 1 : VOL_BATCH;
     for (int64_t base = t0 + threadIdx.x; base < t1; base += BATCH * VOL_WG) {
         double p[BATCH][3][3];
         int64_t vi[BATCH][3];
@@ -180,7 +181,7 @@ __global__ __launch_bounds__(VOL_WG) void k_vol_partial(const double *xyz, const
         for (int r = 0; r < BATCH; r++)
             if (in[r]) s = dd_add(s, vol_term(p[r]));
     }
-    if (!SMALL || t0 + (threadIdx.x & ~63u) < t1)  // (the other waves hold zeros)
+    if (BATCH != 1 || t0 + (threadIdx.x & ~63u) < t1)  // (the other waves hold zeros)
         for (int o = 32; o > 0; o >>= 1) s = dd_add(s, dd_shfl_xor(s, o));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     if (bad) atomicOr(flags, bad);
@@ -222,16 +223,13 @@ void launch_volume(const double *xyz, const int32_t *tri, const int64_t *v_off, 
                    uint32_t *flags, hipStream_t s) {
     hipLaunchKernelGGL(k_vol_clear, dim3(1), dim3(64), 0, s, flags);
     // (a launch takes fewer than 2^32 threads)
-    for (int64_t i0 = 0; i0 < nitems; i0 += VOL_SLICE) {
-        const dim3 grid((unsigned)std::min(nitems - i0, VOL_SLICE));
-        const double rpi = (double)G / (double)nitems;
-        if (max_row <= VOL_WG)
-            hipLaunchKernelGGL(k_vol_partial<true>, grid, dim3(VOL_WG), 0, s, xyz, tri, v_off, t_off, witem, i0, G, rpi,
-                               (DD *)part, flags);
-        else
-            hipLaunchKernelGGL(k_vol_partial<false>, grid, dim3(VOL_WG), 0, s, xyz, tri, v_off, t_off, witem, i0, G, rpi,
-                               (DD *)part, flags);
-    }
+    const auto partial = max_row <= VOL_WG       ? k_vol_partial<1, true>
+                         : max_row <= 2 * VOL_WG ? k_vol_partial<2, true>
+                         : max_row <= VOL_CHUNK  ? k_vol_partial<VOL_BATCH, true>
+                                                 : k_vol_partial<VOL_BATCH, false>;
+    for (int64_t i0 = 0; i0 < nitems; i0 += VOL_SLICE)
+        hipLaunchKernelGGL(partial, dim3((unsigned)std::min(nitems - i0, VOL_SLICE)), dim3(VOL_WG), 0, s, xyz, tri, v_off,
+                           t_off, witem, i0, G, (double)G / (double)nitems, (DD *)part, flags);
     if (G > 0)
         hipLaunchKernelGGL(k_vol_rows, dim3((unsigned)((G + 63) / 64)), dim3(64), 0, s, (const DD *)part, witem, G,
                            vol, flags);

@@ -127,3 +127,19 @@ def test_columns_of_small_rows_equal_the_general_path(ctx):
     longer = _vol(ctx, meshes + [synth.icosphere(2)], True)
     assert np.array_equal(v.view(np.int64), longer[:-1].view(np.int64)) and v[-2] == 1.0
     _check(meshes[:40], v[:40])
+
+
+@pytest.mark.parametrize("most", [257, 511, 512, 513, 1023, 1024, 1025, 4095, 4096])
+def test_columns_of_rows_of_one_item_equal_the_general_path(ctx, most):
+    # rows of at most 512 and of at most 4096 triangles, each a work item, have
+    # variants of their own
+    empty = (np.zeros((0, 3)), np.zeros((0, 3), np.int32))
+    g = np.random.default_rng(most)
+    meshes = [empty]
+    for n in (most, 1, most - 1, 255, 256, most // 2):
+        x = g.normal(size=(n + 2, 3))
+        meshes += [(x, g.integers(0, n + 2, size=(n, 3)).astype(np.int32)), empty, synth.cube((0, 0, 0), 1.0)]
+    v = _vol(ctx, meshes, True)
+    longer = _vol(ctx, meshes + [synth.icosphere(5)], True)
+    assert np.array_equal(v.view(np.int64), longer[:-1].view(np.int64)) and v[-1] == 1.0
+    _check(meshes, v)
