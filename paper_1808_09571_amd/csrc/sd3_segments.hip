@@ -637,19 +637,46 @@ __global__ __launch_bounds__(64, 3) void k_segs(const double *seg, int64_t n, co
                 uu += u[c] * u[c];
                 pu += p[c] * u[c];
             }
-            // a long segment is cut to where the mesh's nearest point can be
-            // (FP32 offsets stay small): the mesh lies within sqrt(3) of the
-            // frame's origin, so within d + 1.75 of the segment (d its
-            // distance to the origin), and a point of it more than d + 3.5
-            // from the origin is farther than that from all of the mesh
-            // (up to 2^26 frame units, where FP64 places the cut to 2^-25)
-            if (uu > 64.0 && uu < 0x1p52 && pp < 0x1p52) {
+            // a long segment is cut (FP32 offsets stay small; up to 2^26 frame
+            // units, where FP64 places a cut, and a pair's distance, to 2^-21)
+            const bool cut = uu < 0x1p52 && pp < 0x1p52;
+            if (MODE == 0 && cut && uu > 64.0) {
+                // to where the mesh's nearest point can be: the mesh lies
+                // within sqrt(3) of the frame's origin, so within d + 1.75 of
+                // the segment (d its distance to the origin), and a point of
+                // it more than d + 3.5 from the origin is farther than that
+                // from all of the mesh
                 const double t = fmin(fmax(-pu / uu, 0.0), 1.0);
                 double d2 = 0.0;
                 for (int c = 0; c < 3; c++) d2 += (p[c] + t * u[c]) * (p[c] + t * u[c]);
                 const double d = sqrt(d2) + 3.5;
                 const double half = sqrt(fmax(d * d - d2, 0.0) / uu) * 1.0001 + 1e-9;
                 const double t0 = fmax(t - half, 0.0), t1 = fmin(t + half, 1.0);
+                for (int c = 0; c < 3; c++) {
+                    p[c] += t0 * u[c];
+                    u[c] *= t1 - t0;
+                }
+            }
+            if (MODE != 0 && cut && uu > 0.25) {
+                // to the mesh's box, wider by the threshold: the nodes' bounds
+                // weaken with the segment's length (through 20,000 loose
+                // triangles, one segment 30 long: the call 167 -> 64 us; 100,000:
+                // 4.00 -> 0.66 ms)
+                double t0 = 0.0, t1 = 1.0;
+                const double e = (MODE == 2 ? r * F.s : 0.0) + 0x1p-16;
+                for (int c = 0; c < 3; c++) {
+                    const double lo = (from_ordered_bits(box[c]) - F.c[c]) * F.s - e;
+                    const double hi = (from_ordered_bits(box[3 + c]) - F.c[c]) * F.s + e;
+                    if (u[c] != 0.0) {
+                        const double x0 = (lo - p[c]) / u[c], x1 = (hi - p[c]) / u[c];
+                        t0 = fmax(t0, fmin(x0, x1));
+                        t1 = fmin(t1, fmax(x0, x1));
+                    } else if (p[c] < lo || p[c] > hi) {
+                        t1 = -1.0;
+                    }
+                }
+                // (nothing of it near: any point of it stands for it)
+                if (!(t0 <= t1)) t0 = t1 = fmin(fmax(-pu / uu, 0.0), 1.0);
                 for (int c = 0; c < 3; c++) {
                     p[c] += t0 * u[c];
                     u[c] *= t1 - t0;
