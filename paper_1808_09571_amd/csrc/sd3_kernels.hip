@@ -2577,8 +2577,10 @@ __global__ __launch_bounds__(64, PREC == 0 && TK <= 64 ? 3 : 1) void k_pairs(con
     // about 8 ns each and set the time of a call whose waves take a few entries
     // (solid columns of 9,000 entries 357 -> 262 us, a 25,000-entry intersects
     // pass 215 -> 112 us); a long one is claimed, since its tile pairs' costs
-    // differ (1.1M entries: 1.52 ms claimed, 1.65 ms dealt out)
-    const bool strided = qcount <= (unsigned)QB * nwave;
+    // differ (1.1M entries: 1.52 ms claimed, 1.65 ms dealt out; from 16 to 32
+    // entries a wave the calls of bodies beside, through and inside each other
+    // take 0.71 to 1.04 of the time dealt out, from 32 to 64 up to 1.09)
+    const bool strided = qcount <= 2u * (unsigned)QB * nwave;
     unsigned long long n_eval = 0, n_boxed = 0, n_tested = 0, n_resc = 0, n_exact = 0, n_bad = 0;
     RescueChunk rch;
     int staged_a = -1;  // the A tile whose copy is in sA (wave-uniform)
