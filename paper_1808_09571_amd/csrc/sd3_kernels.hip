@@ -2816,7 +2816,7 @@ __global__ __launch_bounds__(64, PREC == 0 && TK <= 64 ? 3 : 1) void k_pairs(con
                 n_tested += n;
                 const Tt *pa = sA + a * VS, *pb = sB + b * VS;
                 if constexpr (PREC == 0) {
-                    float fa[F_NTRI32], fb[F_NTRI32];
+                    float fa[F_NTRI], fb[F_NTRI];
                     TriRef<float> TA{fa, 1}, TB{fb, 1};
 #pragma unroll
                     for (int k = 0; k < 9; k++) {
@@ -2866,7 +2866,7 @@ __global__ __launch_bounds__(64, PREC == 0 && TK <= 64 ? 3 : 1) void k_pairs(con
                         n_resc += c == 2;
                     }
                 } else {
-                    double fa[F_NTRI64], fb[F_NTRI64];
+                    double fa[F_NTRI], fb[F_NTRI];
                     TriRef<double> TA{fa, 1}, TB{fb, 1};
 #pragma unroll
                     for (int k = 0; k < 9; k++) {
@@ -3128,7 +3128,7 @@ __device__ void rescue_items(const TriSrc &SA, const TriSrc &SB, RowState *rows,
         int a = e.slots & 0xffff, b = e.slots >> 16;
         // the vertices depend on the entry alone: their loads go out beside
         // the row state's, not after its checks
-        double ta[F_NTRI64], tb[F_NTRI64];
+        double ta[F_NTRI], tb[F_NTRI];
         load_tri64(SA, e.ta, a, ta);
         load_tri64(SB, e.tb, b, tb);
         int g = mA[e.ta].row;

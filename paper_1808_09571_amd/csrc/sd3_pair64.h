@@ -9,9 +9,8 @@
 
 namespace sd3 {
 
-// Per-triangle data, stored as 30 fields read through a strided reference so
-// that the same routine serves LDS tiles (stride K) and private copies
-// (stride 1).
+// Per-triangle data: 30 fields of either type, read through a strided
+// reference.
 enum : int {
     F_V = 0,    // v0 v1 v2 (9)
     F_E = 9,    // e_k = v_{k+1} - v_k (9)
@@ -19,10 +18,7 @@ enum : int {
     F_IE = 21,  // 1/|e_k|^2, 0 for a zero-length edge (3)
     F_G1 = 24,  // dual basis of (v1 - v0, v2 - v0): beta1 = g1 . (p - v0) (3)
     F_G2 = 27,  // beta2 = g2 . (p - v0) (3)
-    F_NTRI64 = 30,
-    F_LO = 30,  // FP32 tiles only: triangle bounding box (3 + 3)
-    F_HI = 33,
-    F_NTRI32 = 36,
+    F_NTRI = 30,
 };
 
 template <typename T>

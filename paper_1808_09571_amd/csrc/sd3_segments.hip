@@ -307,7 +307,7 @@ __global__ __launch_bounds__(64) void k_seg_mesh(const double *xyz, int64_t nv, 
     const int64_t t = blockIdx.x * (int64_t)64 + threadIdx.x;
     const bool in = t < nt;
     double x[9], a[3];
-    double f[F_NTRI64];
+    double f[F_NTRI];
     TriRef<double> R{f, 1};
     const int64_t ti = order[in ? t : nt - 1];
     for (int k = 0; k < 3; k++) {
