@@ -2485,10 +2485,11 @@ __device__ __forceinline__ int wave_gather(Entry &E, const Lists &L, unsigned qc
 }
 
 // Upper bound of the row distance from the smallest FP32 candidate dm of a
-// tile pair (see sd3_pair32.h), rounded up once more for the FP64 compare.
+// tile pair (see sd3_pair32.h), rounded up once more for the FP64 compare (its
+// square may have lost up to 3 * 2^-150 to underflow).
 __device__ __forceinline__ double fp32_upper(float dm, float eu) {
     const double U = sqrt((double)dm) * (1.0 + 4.0 * U32) + (double)eu;
-    return U * (1.0 + 4.0 * U64);
+    return U * (1.0 + 4.0 * U64) + 0x1p-73;
 }
 
 // Whether two point sets are certainly farther apart than lim by their
@@ -2669,7 +2670,8 @@ __global__ __launch_bounds__(64, PREC == 0 && TK <= 64 ? 3 : 1) void k_pairs(con
                 if (PREC == 0) {
                     const double T = (ub + m + eps_c) / (1.0 - 4.0 * U32);
                     const double T2 = T * T * (1.0 + 16.0 * U32);
-                    T2f = T2 < 3.0e38 ? (float)(T2 * (1.0 + 0x1p-20)) : __builtin_inff();
+                    // (the gaps' squares may underflow)
+                    T2f = T2 < 3.0e38 ? (float)(T2 * (1.0 + 0x1p-20)) + 0x1p-140f : __builtin_inff();
                     limf = (float)((ub + m) * (1.0 + 0x1p-20));
                 } else {
                     const double T = (ub + m) * (1.0 + 8.0 * U64);

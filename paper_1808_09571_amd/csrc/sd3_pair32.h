@@ -124,7 +124,9 @@ __device__ __forceinline__ Pair32 pair32(TriRef<float> A, TriRef<float> B, float
             float rz = A[F_V + 3 * k + 2] - B[F_V + 3 * l + 2];
             sep = fminf(sep, bx * rx + by * ry + bz * rz);
         }
-    float lb = best > 0.0f ? sep * __builtin_amdgcn_rsqf(best) - elb : -__builtin_inff();
+    // (below 2^-100 the squares lose bits to underflow, and the reciprocal root
+    // of a denormal is +inf: no bound, the pair goes to the rescue)
+    float lb = best > 0x1p-100f ? sep * __builtin_amdgcn_rsqf(best) - elb : -__builtin_inff();
     return {best, lb};
 }
 
@@ -147,7 +149,8 @@ __device__ __forceinline__ float orient3d_f32(float ax, float ay, float az, floa
 // in the pair's bounding box of extent Ms, so each of the 6 elementary triple
 // products is at most Ms^3 and passes through at most 8 FP32 roundings
 // (48 u Ms^3 < 64 u Ms^3), and moving the 4 points by at most eps each moves
-// the determinant by at most 18 eps Ms^2 + O(eps^2 Ms).
+// the determinant by at most 18 eps Ms^2 + O(eps^2 Ms); underflow adds less than
+// 2^-146.
 // A, B: the corners (9 values); xA, xB: the boxes (lo xyz, hi xyz).
 __device__ __forceinline__ int isect32(const float *A, const float *B, const float *xA, const float *xB,
                                        float eps_c) {
@@ -157,7 +160,8 @@ __device__ __forceinline__ int isect32(const float *A, const float *B, const flo
     ms *= 1.0f + 0x1p-20f;
     const float eo = (24.0f * eps_c * ms * ms + 24.0f * eps_c * eps_c * ms +
                       8.0f * eps_c * eps_c * eps_c + 64.0f * 0x1p-24f * ms * ms * ms) *
-                     (1.0f + 0x1p-16f);
+                         (1.0f + 0x1p-16f) +
+                     0x1p-140f;
     float o[2][3];
 #pragma unroll
     for (int side = 0; side < 2; side++) {

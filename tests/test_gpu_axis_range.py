@@ -114,3 +114,28 @@ def test_scales(ctx, lo, hi, step, tile):
         A += a
         B += b
     _check(ctx, A, B, tile)
+
+
+def _small_rows(seed):
+    """Single triangles that cross, miss each other closely, or lie far apart."""
+    g = np.random.default_rng(seed)
+    A, B = [], []
+    for k in range(60):
+        x, y = g.normal(size=(2, 3, 3))
+        A.append((x, TRI1))
+        B.append((y * 0.5 + [0.0, 0.0, (0.0, 0.5, 2.5)[k % 3]], TRI1))
+    return A, B
+
+
+# the FP32 pass's squares lose bits to underflow from about 2^-50 on, an axis
+# decides nothing below 2^-60, the triple products of the flags are denormal
+# near 2^-44
+@pytest.mark.parametrize("tile", [32, 64, 128])
+@pytest.mark.parametrize("lo,hi,step", [(-56.0, -38.0, 2.0), (-76.0, -57.0, 1.0), (-110.0, -80.0, 10.0)])
+def test_small_scales(ctx, lo, hi, step, tile):
+    A, B = [], []
+    for e in np.arange(lo, hi + step / 2, step):
+        for a, b in (_scale_rows(1.0), _small_rows(int(-e))):
+            A += [(x * 2.0 ** e, t) for x, t in a]
+            B += [(x * 2.0 ** e, t) for x, t in b]
+    _check(ctx, A, B, tile)
