@@ -24,7 +24,9 @@ using namespace sd3;
 // code never passes `scratch` itself to a kernel or a copy (on the host it is
 // only a stand-in for the symbol): it uses the per-device address that
 // hipGetSymbolAddress returns at set-up (scratch_on_device).
-constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)128 << 20;
+// (128 MiB, and the replicas of the counters, so that what fitted beside one
+// copy of them does)
+constexpr size_t NOALLOC_SCRATCH_BYTES = ((size_t)128 << 20) + 4096;
 static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
 
 namespace {
